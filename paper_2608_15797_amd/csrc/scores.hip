@@ -7,26 +7,32 @@
 // token.
 //
 // bf16 caches: the R = G * nq window rows of one (sequence, layer, KV head)
-// form a dense [R x D] x [D x n] contraction, done on MFMA
-// (v_mfma_f32_16x16x16bf16_1k, rows in the M dimension, keys in N). One
-// workgroup per (sequence, layer, KV head); its waves take 16-row blocks of
-// the window rows and make two passes over the keys: the first builds every
-// row's softmax maximum and normaliser (online, per lane, then merged across
-// the 16 lanes holding the same rows), the second recomputes the logits, forms
-// the probabilities and adds their column sums into an LDS accumulator. The
-// accumulator is 64-bit fixed point (each column sum rounded to a multiple of
-// 2^-32, then added with integer atomics), so the total does not depend on
-// the order in which the waves add: the scores are bitwise reproducible. The
-// head's scores are written (or added) once at the end, converted back to
-// float32. The keys stream through
-// an LDS ring shared by the workgroup's eight waves (window_scores_tiled);
-// caches too long for the ring beside the accumulator take the older kernel,
-// in which each wave of four streams K for its own two row blocks.
-//
-// The contraction index d is dealt to lanes so that each lane reads one
-// contiguous quarter of a row: in k-step t, operand element i of lane group
-// q = lane / 16 is d = q * D/4 + 4 t + i, for the q rows (A) and the keys (B)
-// alike.
+// form a dense [R x D] x [D x n] contraction, done on MFMA 16x16x32 bf16, one
+// workgroup of eight waves per head. What bounds it is the exps and the
+// products, which the matrix core and the vector unit do not overlap for this
+// shape (a 16x16x32 product keeps the vector unit from issuing for most of its
+// 16 cycles) and which run at the chip's power limit; so each exp and each
+// vector instruction counts:
+//   - Heads of up to 768 keys (8 waves x 6 tiles of 16 keys in registers) take
+//     one pass: every product and every exp is formed once, and the waves
+//     exchange their rows' partial normalisers through LDS. On the commit
+//     shape (16 x 28 x 4 heads, 896 rows, 641-768 keys) 0.48 ms, against 1.03
+//     for two passes over keys streamed through LDS.
+//   - Longer heads take two passes, the first with the window rows in
+//     registers and the keys streaming (normalisers), the second with the keys
+//     in registers and the rows streaming (column sums): 3.5 ms against 6.2
+//     on 4096 keys.
+//   - No running maximum: a row's exps need no reference as long as its
+//     normaliser stays within 2^-20 .. 2^24, which is tested once per row. A
+//     head with a row outside takes the two passes relative to each row's
+//     maximum, found by a pass of its own.
+// Column sums are float32 over at most 16 rows a lane, then float64 in a
+// fixed order, so the scores are bitwise reproducible and as exact as their
+// float32 result (2.9e-8 in the 2-norm against float64).
+// Measured and not kept: products interleaved one by one with the exps, 32x32
+// products, two or three independent workgroups per CU, four waves per SIMD
+// (all 3.4 to 4.0 ms on 4096 keys, the clock falling from 2.1 to 1.6 GHz as
+// the cycles do).
 //
 // float32 caches take a plain one-wave-per-head kernel (one key per lane).
 #include <hip/hip_runtime.h>
@@ -97,208 +103,10 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void *ptr, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(ptr), (short)0, (int)bytes, 0x00020000);
 }
 
-__device__ __forceinline__ short4_t s4(uint32_t a, uint32_t b) {
-  const uint32_t v[2] = {a, b};
-  return __builtin_bit_cast(short4_t, v);
-}
-
 constexpr float kNegInf = -__builtin_huge_valf();
 
-// Fixed-point column sums of the bf16 kernels: value * 2^32 as int64. A
-// column sum is at most G * nq (every window row's whole probability mass),
-// far below 2^31, and each addend is rounded once (to 2^-33 at worst).
-constexpr double kFix = 4294967296.0;
-__device__ __forceinline__ void fix_add(unsigned long long *acc, float v) {
-  atomicAdd(acc, (unsigned long long)__double2ll_rn((double)v * kFix));
-}
-__device__ __forceinline__ float fix_value(unsigned long long a) {
-  return (float)((double)(long long)a * (1.0 / kFix));
-}
-
-template <int D>
-struct WGeo {
-  static constexpr int QD = D / 4;   // elements per lane quarter of a row
-  static constexpr int KS = D / 16;  // MFMA k-steps over D
-  static constexpr int NV = QD / 8;  // 16-byte vectors per quarter
-};
-
-// Quarter q of row `row` of a [rows][D] bf16 array; zero past the resource.
-template <int D>
-__device__ __forceinline__ void load_quarter(rsrc_t r, int row, int q, u32x4 (&v)[WGeo<D>::NV]) {
-  const uint32_t off = ((uint32_t)row * D + (uint32_t)q * WGeo<D>::QD) * 2u;
-#pragma unroll
-  for (int i = 0; i < WGeo<D>::NV; i++) v[i] = __builtin_amdgcn_raw_buffer_load_b128(r, off + 16u * i, 0, 0);
-}
-
-// Operand of k-step t from a loaded quarter: elements 4t .. 4t+3.
-template <int D>
-__device__ __forceinline__ short4_t kstep_op(const u32x4 (&v)[WGeo<D>::NV], int t) {
-  const u32x4 w = v[t >> 1];
-  return (t & 1) ? s4(w.z, w.w) : s4(w.x, w.y);
-}
-
-constexpr int kRB = 2;  // 16-row blocks per wave at a time
-
-template <int D>
-__device__ __forceinline__ void logits_tile(const short4_t (&qa)[kRB][WGeo<D>::KS],
-                                            const u32x4 (&kv)[WGeo<D>::NV], float4_t (&c)[kRB]) {
-#pragma unroll
-  for (int b = 0; b < kRB; b++) c[b] = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int t = 0; t < WGeo<D>::KS; t++) {
-    const short4_t kb = kstep_op<D>(kv, t);
-#pragma unroll
-    for (int b = 0; b < kRB; b++) c[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qa[b][t], kb, c[b], 0, 0, 0);
-  }
-}
-
-template <int D, int NRB>
-__device__ __forceinline__ void logits_tile_n(const short4_t (&qa)[NRB][WGeo<D>::KS],
-                                              const u32x4 (&kv)[WGeo<D>::NV], float4_t (&c)[NRB]) {
-#pragma unroll
-  for (int b = 0; b < NRB; b++) c[b] = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int t = 0; t < WGeo<D>::KS; t++) {
-    const short4_t kb = kstep_op<D>(kv, t);
-#pragma unroll
-    for (int b = 0; b < NRB; b++) c[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qa[b][t], kb, c[b], 0, 0, 0);
-  }
-}
-
-template <int D>
-__global__ __launch_bounds__(256) void window_scores_bf16(ScoreParams p) {
-  extern __shared__ unsigned long long acc[];  // [cap] fixed-point column sums
-  const int unit = blockIdx.x;
-  const int h = unit % p.Hkv;
-  const int sl = unit / p.Hkv;
-  const int l = sl % p.L;
-  const int s = sl / p.L;
-  const int tid = threadIdx.x;
-  const int wave = tid / kWave;
-  const int lane = tid % kWave;
-  const int gq = lane >> 4, col = lane & 15;
-  int n = p.len[s];
-  n = n < 0 ? 0 : (n > p.cap ? p.cap : n);
-  for (int j = tid; j < n; j += blockDim.x) acc[j] = 0ull;
-  __syncthreads();
-
-  const int R = p.G * p.nq;
-  const bf16_t *Q = static_cast<const bf16_t *>(p.q_win) + (((size_t)s * p.L + l) * p.Hq + (size_t)h * p.G) * p.nq * D;
-  const bf16_t *K = static_cast<const bf16_t *>(p.k) + (size_t)unit * p.cap * D;
-  const rsrc_t qr = make_rsrc(Q, (uint32_t)R * D * 2u);
-  const rsrc_t kr = make_rsrc(K, (uint32_t)n * D * 2u);
-  const float c = p.scale * kLog2e;
-  const int tiles = (n + 15) / 16;
-  const int blocks = (R + 15) / 16;
-
-  for (int rb = wave * kRB; rb < blocks; rb += 4 * kRB) {
-    short4_t qa[kRB][WGeo<D>::KS];
-    int nr[kRB][4];
-#pragma unroll
-    for (int b = 0; b < kRB; b++) {
-      u32x4 v[WGeo<D>::NV];
-      load_quarter<D>(qr, (rb + b) * 16 + col, gq, v);
-#pragma unroll
-      for (int t = 0; t < WGeo<D>::KS; t++) qa[b][t] = kstep_op<D>(v, t);
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int row = (rb + b) * 16 + 4 * gq + i;  // output row of this lane
-        const int r = row % p.nq;
-        nr[b][i] = row < R ? n - (p.nq - 1 - r) : 0;
-      }
-    }
-    // Pass 1: per-row maximum and normaliser over the visible keys.
-    float m[kRB][4], z[kRB][4];
-#pragma unroll
-    for (int b = 0; b < kRB; b++)
-#pragma unroll
-      for (int i = 0; i < 4; i++) { m[b][i] = kNegInf; z[b][i] = 0.f; }
-    u32x4 kv[WGeo<D>::NV];
-    if (tiles > 0) load_quarter<D>(kr, col, gq, kv);
-    for (int kt = 0; kt < tiles; kt++) {
-      u32x4 cur[WGeo<D>::NV];
-#pragma unroll
-      for (int i = 0; i < WGeo<D>::NV; i++) cur[i] = kv[i];
-      if (kt + 1 < tiles) load_quarter<D>(kr, (kt + 1) * 16 + col, gq, kv);
-      float4_t cc[kRB];
-      logits_tile<D>(qa, cur, cc);
-      const int j = kt * 16 + col;
-#pragma unroll
-      for (int b = 0; b < kRB; b++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          if (j < nr[b][i]) {
-            const float x = cc[b][i] * c;
-            if (x > m[b][i]) {
-              z[b][i] = z[b][i] * fast_exp2(m[b][i] - x) + 1.f;
-              m[b][i] = x;
-            } else {
-              z[b][i] += fast_exp2(x - m[b][i]);
-            }
-          }
-        }
-    }
-    // Merge the 16 lanes that hold the same rows (lane bits 0..3).
-#pragma unroll
-    for (int msk = 1; msk <= 8; msk <<= 1)
-#pragma unroll
-      for (int b = 0; b < kRB; b++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const float om = shfl_xor(m[b][i], msk);
-          const float oz = shfl_xor(z[b][i], msk);
-          const float M = fmaxf(m[b][i], om);
-          float zz = 0.f;
-          if (z[b][i] > 0.f) zz += z[b][i] * fast_exp2(m[b][i] - M);
-          if (oz > 0.f) zz += oz * fast_exp2(om - M);
-          m[b][i] = M;
-          z[b][i] = zz;
-        }
-    float iz[kRB][4];
-#pragma unroll
-    for (int b = 0; b < kRB; b++)
-#pragma unroll
-      for (int i = 0; i < 4; i++) iz[b][i] = z[b][i] > 0.f ? 1.0f / z[b][i] : 0.f;
-    // Pass 2: probabilities, column sums into the LDS accumulator.
-    if (tiles > 0) load_quarter<D>(kr, col, gq, kv);
-    for (int kt = 0; kt < tiles; kt++) {
-      u32x4 cur[WGeo<D>::NV];
-#pragma unroll
-      for (int i = 0; i < WGeo<D>::NV; i++) cur[i] = kv[i];
-      if (kt + 1 < tiles) load_quarter<D>(kr, (kt + 1) * 16 + col, gq, kv);
-      float4_t cc[kRB];
-      logits_tile<D>(qa, cur, cc);
-      const int j = kt * 16 + col;
-      float cs = 0.f;
-#pragma unroll
-      for (int b = 0; b < kRB; b++)
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-          if (j < nr[b][i] && iz[b][i] > 0.f) cs += fast_exp2(cc[b][i] * c - m[b][i]) * iz[b][i];
-      cs += shfl_xor(cs, 16);
-      cs += shfl_xor(cs, 32);
-      if (gq == 0 && j < n) fix_add(&acc[j], cs);
-    }
-  }
-  __syncthreads();
-  float *sc = p.scores + (size_t)unit * p.cap;
-  for (int j = tid; j < n; j += blockDim.x) sc[j] = p.accumulate ? sc[j] + fix_value(acc[j]) : fix_value(acc[j]);
-}
-
-// LDS-tiled variant. A workgroup of NW waves holds NW * KRB 16-row blocks of
-// the window rows at a time (the A operands in registers) and streams the
-// head's keys through a two-tile LDS ring: each tile of kTK keys is brought in
-// once per workgroup by buffer-to-LDS loads spread over the waves, then read
-// by every wave. K is so read twice (two passes) per group of NW * KRB * 16
-// rows, instead of twice per two row blocks per wave. A tile row of D bf16 is
-// stored with its 16-byte units swizzled (unit c at c ^ (row mod D/8)), so the
-// operand reads (16 keys x one unit each) hit distinct banks. The kernel is
-// bound by its arithmetic (two exps per row and key): with NW = 8, KRB = 2
-// (4 waves per SIMD) measured fastest, ahead of fewer K passes at KRB = 4.
-// The key loads keep the default cache policy: the second pass finds the
-// head's keys in L2 (the streaming hint measured 2% slower).
-constexpr int kTK = 32;  // keys per LDS tile
-constexpr float kSlack = 8.0f;  // log2 units the first pass's reference may trail its maximum
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) void lds_void_t;
 
 // s_waitcnt vmcnt(n), other counters unconstrained.
 template <int N>
@@ -306,212 +114,442 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-typedef __attribute__((address_space(3))) void lds_void_t;
+__device__ __forceinline__ float4_t mfma(u32x4 a, u32x4 b, float4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
+                                                 0, 0, 0);
+}
 
-template <int D, int NW, int KRB>
-__global__ __launch_bounds__(NW * 64) void window_scores_tiled(ScoreParams p) {
-  constexpr int RU = D / 8;             // 16-byte units per key row
-  constexpr int TB = kTK * D * 2;       // bytes per tile
-  constexpr int NI = TB / 1024;         // 1 KiB buffer-to-LDS loads per tile
-  constexpr int RPI = 1024 / (D * 2);   // key rows per load
-  extern __shared__ float smem[];
-  unsigned long long *acc = reinterpret_cast<unsigned long long *>(smem);  // [cap] fixed-point column sums
+__device__ __forceinline__ float recip(float z) {
+  const float r = __builtin_amdgcn_rcpf(z);
+  return fmaf(fmaf(-z, r, 1.0f), r, r);
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E;  // quad_perm [1,0,3,2] and [2,3,0,1]
+constexpr int kHalfMirror = 0x141, kMirror = 0x140;
+
+// Sum (or maximum) over the 16 lanes of a row of lanes, in every one of them.
+template <bool MAX>
+__device__ __forceinline__ float reduce16(float v) {
+  auto op = [](float a, float b) { return MAX ? fmaxf(a, b) : a + b; };
+  v = op(v, dpp<kXor1>(v));
+  v = op(v, dpp<kXor2>(v));
+  v = op(v, dpp<kHalfMirror>(v));
+  return op(v, dpp<kMirror>(v));
+}
+
+// Sum of the lanes l, l^16, l^32, l^48, in every one of them.
+__device__ __forceinline__ float sum_groups(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+constexpr int kNW = 8;           // waves per workgroup
+constexpr int kKeyTiles = 6;     // 16-key tiles a wave holds at once
+constexpr int kRowTiles = 7;     // 16-row tiles a wave holds at once (pass 1 of two)
+constexpr int kRG = kNW * kRowTiles * 16;  // window rows per group (two passes)
+constexpr int kFlush = 8;        // blocks of 32 rows between the float32 column sums' flushes
+// A row's exponentials are taken without a reference while its normaliser
+// lies in this range: its largest logit is then between about -30 and 24
+// (log2), so the float32 exponents lose nothing against a maximum-relative
+// form, and nothing that counts underflows.
+constexpr float kZLow = 0x1p-20f, kZHigh = 0x1p24f;
+
+template <int D>
+struct WLds {
+  static constexpr int RU = D / 8;              // 16-byte units per row
+  static constexpr int SLOT = 32 * D * 2;       // bytes per ring slot
+  char ring[2][SLOT];
+  double sum[kKeyTiles][kNW * kWave];  // the lanes' column sums
+  union {
+    float z[2][32][36];                // one pass: per row, the partial normalisers of 8 waves x 4 lanes
+    struct {
+      int nr[kRG];                     // two passes, per row of the group: the keys it sees,
+      float f[kRG], m[kRG];            // 1 / normaliser and reference
+    } g;
+  };
+  int bad;
+};
+
+// The window scores of one (sequence, layer, KV head) of n keys and R window
+// rows by kNW waves. One operand of the products stays in a wave's registers
+// (16-row tiles wave + kNW * k, the M dimension), the other streams through an
+// LDS ring in blocks of 32, shared by the waves (halves of 16, the N
+// dimension). A lane then holds N index lane & 15 and M index 4 * (lane >> 4)
+// + i of each tile.
+template <int D>
+struct Window {
+  static constexpr int KS = D / 32;  // MFMA k-steps
+  static constexpr int RU = WLds<D>::RU;
+  static constexpr int NI = WLds<D>::SLOT / 1024;  // 1 KiB loads per ring slot
+
+  const ScoreParams &p;
+  WLds<D> &lds;
+  rsrc_t qr, kr;
+  int n, R, wave, lane;
+  float c;
+  float *sc;
+
+  // A copy whose lane number the compiler cannot follow, so that the address
+  // arithmetic of one variant is not kept in registers through the others.
+  __device__ __forceinline__ Window fresh() const {
+    Window w = *this;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(w.lane));
+#endif
+    return w;
+  }
+
+  // Workgroup barrier without the fence of __syncthreads (whose release
+  // would also wait for the ring loads in flight): this wave's LDS
+  // operations are complete, its ring loads are waited for explicitly, and
+  // the memory clobber keeps the compiler from moving accesses across it.
+  __device__ __forceinline__ void bar() const {
+    __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
+    asm volatile("s_barrier" ::: "memory");
+  }
+
+  // Rows row0 .. row0 + 31 of r's array into a ring slot, 16-byte unit u of
+  // row r at u ^ (r mod RU), spread over the waves; zeros past the array.
+  __device__ __forceinline__ void issue(rsrc_t r, int row0, int slot) const {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if (NI >= kNW || wave < NI) {
+      const int row = wave * (1024 / (D * 2)) + lane / RU;
+      const int u = (lane % RU) ^ (row % RU);
+      const uint32_t off = ((uint32_t)(row0 + row) * RU + (uint32_t)u) * 16u;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t *)(lds.ring[slot] + wave * 1024), 16, off, 0, 0, 0);
+    }
+#else
+    (void)r;  // the host pass has no buffer-to-LDS loads
+    (void)row0;
+    (void)slot;
+    (void)RU;
+    (void)NI;
+#endif
+  }
+
+  // The wave's M tiles k0 .. k0 + T - 1 of r's array from row base.
+  template <int T>
+  __device__ __forceinline__ void load_tiles(u32x4 (&mf)[T][KS], rsrc_t r, int base, int k0) const {
+#pragma unroll
+    for (int k = 0; k < T; k++) {
+      const uint32_t off = (uint32_t)(base + (wave + kNW * (k0 + k)) * 16 + (lane & 15)) * (D * 2) +
+                           (uint32_t)(lane >> 4) * 16u;
+#pragma unroll
+      for (int t = 0; t < KS; t++) mf[k][t] = __builtin_amdgcn_raw_buffer_load_b128(r, off + 64u * t, 0, 0);
+    }
+  }
+
+  // Products of half b of a ring slot with the wave's tiles.
+  template <int T>
+  __device__ __forceinline__ void products(const u32x4 (&mf)[T][KS], int slot, int b, float4_t (&a)[T]) const {
+    const int row = 16 * b + (lane & 15);
+    u32x4 q[KS];
+#pragma unroll
+    for (int t = 0; t < KS; t++)
+      q[t] = *reinterpret_cast<const u32x4 *>(lds.ring[slot] + (row * RU + ((4 * t + (lane >> 4)) ^ (row % RU))) * 16);
+#pragma unroll
+    for (int k = 0; k < T; k++) {
+      a[k] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < KS; t++) a[k] = mfma(mf[k][t], q[t], a[k]);
+    }
+  }
+
+  // Column sums: a lane's float32 sums of 4 T keys, each over at most 2 kFlush
+  // rows, are summed over quads of lanes (lane l of a quad keeps key l of each
+  // tile's four) and added in float64.
+  template <int T>
+  __device__ __forceinline__ void flush(float4_t (&acc)[T]) const {
+    const bool b0 = lane & 1, b1 = lane & 2;
+#pragma unroll
+    for (int k = 0; k < T; k++) {
+      const float s01 = (b0 ? acc[k][1] : acc[k][0]) + dpp<kXor1>(b0 ? acc[k][0] : acc[k][1]);
+      const float s23 = (b0 ? acc[k][3] : acc[k][2]) + dpp<kXor1>(b0 ? acc[k][2] : acc[k][3]);
+      lds.sum[k][threadIdx.x] += (double)((b1 ? s23 : s01) + dpp<kXor2>(b1 ? s01 : s23));
+      acc[k] = float4_t{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+
+  template <int T>
+  __device__ __forceinline__ void clear(float4_t (&acc)[T]) const {
+#pragma unroll
+    for (int k = 0; k < T; k++) {
+      acc[k] = float4_t{0.f, 0.f, 0.f, 0.f};
+      lds.sum[k][threadIdx.x] = 0.0;
+    }
+  }
+
+  // The quads' sums, written by the first; `add`: to the stored scores.
+  template <int T>
+  __device__ __forceinline__ void put(int k0, bool add) const {
+#pragma unroll
+    for (int k = 0; k < T; k++) {
+      double v = lds.sum[k][threadIdx.x];
+      v += shfl_xor(v, 4);
+      v += shfl_xor(v, 8);
+      const int j = (wave + kNW * (k0 + k)) * 16 + 4 * (lane >> 4) + (lane & 15);
+      if ((lane & 15) < 4 && j < n) sc[j] = add ? sc[j] + (float)v : (float)v;
+    }
+  }
+
+  // Keys that window row rho sees (0 past the last row).
+  __device__ __forceinline__ int visible(int rho) const {
+    const int late = p.nq - 1 - (int)((uint32_t)rho % (uint32_t)p.nq);
+    return rho < R ? n - late : 0;
+  }
+
+  // One pass: every key of the head in the waves' registers, the window rows
+  // streaming. Per block of 32 rows the waves exchange their partial
+  // normalisers through LDS and add the probabilities, each formed once, to
+  // the column sums. The last MS tiles may hold keys a row does not see.
+  // False, with nothing written, where a row leaves the range of the
+  // reference-free form.
+  template <int T, int MS>
+  __device__ __forceinline__ bool one_pass() const {
+    const int gq = lane >> 4, r16 = lane & 15;
+    u32x4 kf[T][KS];
+    load_tiles<T>(kf, kr, 0, 0);
+    float4_t acc[T];
+    clear<T>(acc);
+    const int blocks = (R + 31) / 32;
+    bool bad = false;
+    issue(qr, 0, 0);
+    wait_vm<0>();
+    bar();
+#pragma unroll 1
+    for (int blk = 0; blk < blocks; blk++) {
+      issue(qr, (blk + 1) * 32, (blk + 1) & 1);  // past the last row: zeros, no memory traffic
+      float4_t x[2][T];
+      int nr[2];
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        nr[b] = visible(blk * 32 + 16 * b + r16);
+        products<T>(kf, blk & 1, b, x[b]);
+      }
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        float4_t z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < T; k++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) {
+            float v = fast_exp2(x[b][k][i] * c);
+            if (k >= T - MS) v = (wave + kNW * k) * 16 + 4 * gq + i < nr[b] ? v : 0.f;
+            x[b][k][i] = v;
+            z[i] += v;
+          }
+        lds.z[blk & 1][16 * b + r16][4 * wave + gq] = (z[0] + z[1]) + (z[2] + z[3]);
+      }
+      wait_vm<0>();
+      bar();
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        // This lane adds 8 of the row's 32 partials, then the four groups.
+        const float *zr = lds.z[blk & 1][16 * b + r16] + 8 * gq;
+        const float4_t za = *reinterpret_cast<const float4_t *>(zr), zb = *reinterpret_cast<const float4_t *>(zr + 4);
+        const float Z = sum_groups(((za[0] + za[1]) + (za[2] + za[3])) + ((zb[0] + zb[1]) + (zb[2] + zb[3])));
+        bad |= nr[b] > 0 && !(Z >= kZLow && Z <= kZHigh);
+        const float f = nr[b] > 0 ? recip(Z) : 0.f;
+#pragma unroll
+        for (int k = 0; k < T; k++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) acc[k][i] = fmaf(x[b][k][i], f, acc[k][i]);
+      }
+      if (blk % kFlush == kFlush - 1) flush<T>(acc);
+    }
+    flush<T>(acc);
+    bar();  // every wave's reads are done
+    // The waves hold the same normalisers, so they agree.
+    if (__builtin_amdgcn_ballot_w64(bad) != 0) return false;
+    put<T>(0, p.accumulate != 0);
+    return true;
+  }
+
+  // Two passes: `blocks` blocks of 32 rows of r's array from row0 through the
+  // ring, eat(h, a) for the products of each half h (unscaled). Block i + 1 is
+  // loaded while block i is read; the rows past the array are zeros.
+  template <int T, typename Eat>
+  __device__ __forceinline__ void stream(const u32x4 (&mf)[T][KS], rsrc_t r, int row0, int blocks, Eat eat) const {
+    issue(r, row0, 0);
+#pragma unroll 1
+    for (int i = 0; i < blocks; i++) {
+      wait_vm<0>();
+      bar();
+      issue(r, row0 + (i + 1) * 32, (i + 1) & 1);
+      float4_t a[2][T];
+#pragma unroll
+      for (int b = 0; b < 2; b++) products<T>(mf, i & 1, b, a[b]);
+#pragma unroll
+      for (int b = 0; b < 2; b++) eat(2 * i + b, a[b]);
+    }
+    wait_vm<0>();
+    bar();  // every wave's reads of the ring are done
+  }
+
+  // Pass 1 over the keys, with the group's row tiles t0 + wave + kNW * k in
+  // the waves' registers: each row's normaliser. MODE 0: without a reference;
+  // 1: each row's maximum, into lds.g.m; 2: relative to it.
+  template <int T, int MODE>
+  __device__ __forceinline__ void normalisers(int row0, int t0) const {
+    const int gq = lane >> 4, r16 = lane & 15;
+    u32x4 qf[T][KS];
+    load_tiles<T>(qf, qr, row0 + 16 * t0, 0);
+    auto at = [&](int k) { return (t0 + wave + kNW * k) * 16 + 4 * gq; };
+    float4_t z[T], m[MODE == 2 ? T : 1];
+#pragma unroll
+    for (int k = 0; k < T; k++) {
+      z[k] = MODE == 1 ? float4_t{kNegInf, kNegInf, kNegInf, kNegInf} : float4_t{0.f, 0.f, 0.f, 0.f};
+      if (MODE == 2) m[k] = *reinterpret_cast<const float4_t *>(lds.g.m + at(k));
+    }
+    auto fold = [&](int k, int i, float a, bool sees) {
+      float x = MODE == 2 ? fmaf(a, c, -m[MODE == 2 ? k : 0][i]) : a * c;
+      if (!sees) x = kNegInf;
+      if (MODE == 1) z[k][i] = fmaxf(z[k][i], x);
+      else z[k][i] += fast_exp2(x);
+    };
+    // Blocks of keys that every row sees, then the others with the mask.
+    const int seen = n - p.nq + 1;
+    const int plain = seen > 0 ? seen / 32 : 0, all = (n + 31) / 32;
+    if (plain > 0)
+      stream<T>(qf, kr, 0, plain, [&](int, const float4_t (&a)[T]) {
+#pragma unroll
+        for (int k = 0; k < T; k++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) fold(k, i, a[k][i], true);
+      });
+    if (all > plain)
+      stream<T>(qf, kr, plain * 32, all - plain, [&](int h, const float4_t (&a)[T]) {
+        const int key = (plain * 2 + h) * 16 + r16;
+#pragma unroll
+        for (int k = 0; k < T; k++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) fold(k, i, a[k][i], key < lds.g.nr[at(k) + i]);
+      });
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < T; k++) {
+      float4_t v;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        v[i] = reduce16<MODE == 1>(z[k][i]);
+        const bool live = lds.g.nr[at(k) + i] > 0;
+        if (MODE == 0) bad |= live && !(v[i] >= kZLow && v[i] <= kZHigh);
+        if (MODE == 1) v[i] = live && v[i] > kNegInf ? v[i] : 0.f;
+        else v[i] = live && v[i] > 0.f ? recip(v[i]) : 0.f;
+      }
+      if (r16 == 0) *reinterpret_cast<float4_t *>((MODE == 1 ? lds.g.m : lds.g.f) + at(k)) = v;
+    }
+    if (MODE == 0 && bad) lds.bad = 1;
+  }
+
+  template <int MODE>
+  __device__ __forceinline__ void normalise(int row0, int tiles) const {
+    const int slots = (tiles + kNW - 1) / kNW;  // per wave, at most kRowTiles
+    if (MODE == 0) {
+      if (slots <= 2) fresh().template normalisers<2, 0>(row0, 0);
+      else if (slots <= 4) fresh().template normalisers<4, 0>(row0, 0);
+      else fresh().template normalisers<kRowTiles, 0>(row0, 0);
+    } else {
+#pragma unroll 1
+      for (int k = 0; k < slots; k++) fresh().template normalisers<1, MODE>(row0, kNW * k);
+    }
+    bar();
+  }
+
+  // Pass 2, over the group's rows with tiles k0 .. k0 + T - 1 of the keys in
+  // the waves' registers: their column sums.
+  template <int T, bool MASK>
+  __device__ __forceinline__ void columns(int row0, int blocks, int k0) const {
+    const int gq = lane >> 4, r16 = lane & 15;
+    u32x4 kf[T][KS];
+    load_tiles<T>(kf, kr, 0, k0);
+    float4_t acc[T];
+    clear<T>(acc);
+    stream<T>(kf, qr, row0, blocks, [&](int h, const float4_t (&a)[T]) {
+      const float f = lds.g.f[16 * h + r16], m = lds.g.m[16 * h + r16];
+      const int nr = MASK ? lds.g.nr[16 * h + r16] : 0;
+#pragma unroll
+      for (int k = 0; k < T; k++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          float x = fmaf(a[k][i], c, -m);
+          if (MASK) x = (wave + kNW * (k0 + k)) * 16 + 4 * gq + i < nr ? x : kNegInf;
+          acc[k][i] = fmaf(fast_exp2(x), f, acc[k][i]);
+        }
+      if (h % (2 * kFlush) == 2 * kFlush - 1) flush<T>(acc);
+    });
+    flush<T>(acc);
+    put<T>(k0, p.accumulate != 0 || row0 > 0);
+  }
+
+  __device__ __forceinline__ void two_pass(int slots) const {
+    const int groups = (R + kRG - 1) / kRG;
+    const int per = ((R + groups - 1) / groups + 31) / 32 * 32;  // rows per group, at most kRG
+    const int seen = n - p.nq + 1;  // keys below this are visible to every row
+#pragma unroll 1
+    for (int row0 = 0; row0 < R; row0 += per) {
+      const int rows = R - row0 < per ? R - row0 : per;
+      const int blocks = (rows + 31) / 32;
+      if (threadIdx.x == 0) lds.bad = 0;
+      for (int at = threadIdx.x; at < kRG; at += kNW * kWave) {
+        lds.g.nr[at] = at < rows ? visible(row0 + at) : 0;
+        lds.g.f[at] = lds.g.m[at] = 0.f;
+      }
+      bar();
+      normalise<0>(row0, 2 * blocks);
+      if (lds.bad) {
+        normalise<1>(row0, 2 * blocks);
+        normalise<2>(row0, 2 * blocks);
+      }
+#pragma unroll 1
+      for (int k0 = 0; k0 < slots; k0 += kKeyTiles) {
+        const int kt = slots - k0;
+        // Uniform over the workgroup (every wave meets the barriers inside).
+        const bool mask = kNW * (k0 + kKeyTiles) * 16 > seen;
+        if (kt <= 2) fresh().template columns<2, true>(row0, blocks, k0);
+        else if (kt <= 4) fresh().template columns<4, true>(row0, blocks, k0);
+        else if (mask) fresh().template columns<kKeyTiles, true>(row0, blocks, k0);
+        else fresh().template columns<kKeyTiles, false>(row0, blocks, k0);
+      }
+    }
+  }
+};
+
+template <int D>
+__global__ __launch_bounds__(kNW * 64) __attribute__((amdgpu_waves_per_eu(2))) void window_scores_bf16(ScoreParams p) {
+  __shared__ __align__(16) WLds<D> lds;
   const int unit = blockIdx.x;
   const int h = unit % p.Hkv;
   const int sl = unit / p.Hkv;
   const int l = sl % p.L;
   const int s = sl / p.L;
-  const int tid = threadIdx.x;
-  const int wave = tid / kWave;
-  const int lane = tid % kWave;
-  const int gq = lane >> 4, col = lane & 15;
   int n = p.len[s];
   n = n < 0 ? 0 : (n > p.cap ? p.cap : n);
-  char *ring = reinterpret_cast<char *>(acc + ((p.cap + 1) & ~1));  // [2][TB], 16-byte aligned
-  for (int j = tid; j < n; j += NW * kWave) acc[j] = 0ull;
-  __syncthreads();
-
+  if (n == 0) return;
   const int R = p.G * p.nq;
   const bf16_t *Q = static_cast<const bf16_t *>(p.q_win) + (((size_t)s * p.L + l) * p.Hq + (size_t)h * p.G) * p.nq * D;
   const bf16_t *K = static_cast<const bf16_t *>(p.k) + (size_t)unit * p.cap * D;
-  const rsrc_t qr = make_rsrc(Q, (uint32_t)R * D * 2u);
-  const rsrc_t kr = make_rsrc(K, (uint32_t)n * D * 2u);
-  const float c = p.scale * kLog2e;
-  const int tiles = (n + kTK - 1) / kTK;
-  const int blocks = (R + 15) / 16;
-  // This wave's share of a tile's loads: instructions I = wave, wave + NW, ...
-  const int mine = (NI - wave + NW - 1) / NW;
-
-  // Tile kt into ring slot kt & 1: load I covers key rows RPI*I .. RPI*I + RPI - 1;
-  // lane l writes LDS unit l of the load, which holds key row RPI*I + l / RU,
-  // unit (l % RU) ^ (row % RU) of the row.
-  auto issue = [&](int kt) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    char *slot = ring + (kt & 1) * TB;
-    for (int I = wave; I < NI; I += NW) {
-      const int row = RPI * I + lane / RU;
-      const int u = (lane % RU) ^ (row % RU);
-      const uint32_t off = ((uint32_t)(kt * kTK + row) * RU + (uint32_t)u) * 16u;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lds_void_t *)(slot + I * 1024), 16, off, 0, 0, 0);
-    }
-#else
-    (void)kt;  // the host pass has no buffer-to-LDS loads
-    (void)kr;
-    (void)RPI;
-#endif
-  };
-  // Wait for this wave's loads of the current tile, with `next` of its loads
-  // (those of the following tile) allowed to stay in flight.
-  auto wait_mine = [&](int next) {
-    if (next >= 2) wait_vm<2>();
-    else if (next == 1) wait_vm<1>();
-    else wait_vm<0>();
-  };
-  // Operand of 16 keys (subtile st of the tile in `slot`): quarter gq of key
-  // row st*16 + col, as kv[NV] 16-byte units.
-  auto read_kv = [&](const char *slot, int st, u32x4 (&kv)[WGeo<D>::NV]) {
-    const int row = st * 16 + col;
-#pragma unroll
-    for (int i = 0; i < WGeo<D>::NV; i++) {
-      const int u = (gq * WGeo<D>::NV + i) ^ (row % RU);
-      kv[i] = *reinterpret_cast<const u32x4 *>(slot + (row * RU + u) * 16);
-    }
-  };
-  // Workgroup barrier without the fence of __syncthreads (whose release
-  // would also wait for the next tile's loads in flight): this wave's LDS
-  // operations are complete, its tile loads are waited for by wait_mine, and
-  // the memory clobber keeps the compiler from moving accesses across it.
-  auto bar = [&]() {
-    __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
-    asm volatile("s_barrier" ::: "memory");
-  };
-  // One pass over the keys through the ring; body(kv, key0) per subtile.
-  auto stream = [&](auto body) {
-    if (tiles > 0) issue(0);
-    for (int kt = 0; kt < tiles; kt++) {
-      const bool more = kt + 1 < tiles;
-      if (more) issue(kt + 1);
-      wait_mine(more ? mine : 0);
-      bar();  // every wave's loads of tile kt have landed
-      const char *slot = ring + (kt & 1) * TB;
-#pragma unroll
-      for (int st = 0; st < kTK / 16; st++) {
-        u32x4 kv[WGeo<D>::NV];
-        read_kv(slot, st, kv);
-        body(kv, kt * kTK + st * 16);
-      }
-      bar();  // every wave is done with slot kt & 1 before it is refilled
-    }
-  };
-
-  for (int g0 = 0; g0 < blocks; g0 += NW * KRB) {
-    const int rb = g0 + wave * KRB;
-    short4_t qa[KRB][WGeo<D>::KS];
-    int nr[KRB][4];
-#pragma unroll
-    for (int b = 0; b < KRB; b++) {
-      u32x4 v[WGeo<D>::NV];
-      load_quarter<D>(qr, (rb + b) * 16 + col, gq, v);
-#pragma unroll
-      for (int t = 0; t < WGeo<D>::KS; t++) qa[b][t] = kstep_op<D>(v, t);
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int row = (rb + b) * 16 + 4 * gq + i;  // output row of this lane
-        const int r = row % p.nq;
-        nr[b][i] = row < R ? n - (p.nq - 1 - r) : 0;
-      }
-    }
-    // Pass 1: per-row maximum and normaliser over the visible keys. The
-    // reference m may trail the running maximum by up to kSlack (every term
-    // 2^(x - m) stays below 2^kSlack and exact to fp32 rounding), so almost
-    // every key costs one exp and no divergent rescale; the merge below
-    // settles each row on its true maximum.
-    float m[KRB][4], z[KRB][4];
-#pragma unroll
-    for (int b = 0; b < KRB; b++)
-#pragma unroll
-      for (int i = 0; i < 4; i++) { m[b][i] = kNegInf; z[b][i] = 0.f; }
-    const bool active = rb < blocks;  // wave-uniform: rows of this wave exist
-    stream([&](const u32x4 (&kv)[WGeo<D>::NV], int key0) {
-      if (!active) return;
-      float4_t cc[KRB];
-      logits_tile_n<D, KRB>(qa, kv, cc);
-      const int j = key0 + col;
-      float x[KRB][4];
-      bool up = false;
-#pragma unroll
-      for (int b = 0; b < KRB; b++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          x[b][i] = j < nr[b][i] ? cc[b][i] * c : kNegInf;
-          up |= x[b][i] > m[b][i] + kSlack;
-        }
-      // The reference moves on the wave's first keys and then rarely: test
-      // it for the whole wave, so that the rescale (an exp of its own, which
-      // the compiler otherwise issues under a lane mask for every key) is
-      // skipped by a uniform branch.
-      if (__builtin_amdgcn_ballot_w64(up) != 0) {
-#pragma unroll
-        for (int b = 0; b < KRB; b++)
-#pragma unroll
-          for (int i = 0; i < 4; i++)
-            if (x[b][i] > m[b][i] + kSlack) {
-              z[b][i] = z[b][i] > 0.f ? z[b][i] * fast_exp2(m[b][i] - x[b][i]) : 0.f;
-              m[b][i] = x[b][i];
-            }
-      }
-#pragma unroll
-      for (int b = 0; b < KRB; b++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) z[b][i] += fast_exp2(fmaxf(x[b][i] - m[b][i], -256.0f));
-    });
-    // Merge the 16 lanes that hold the same rows (lane bits 0..3).
-#pragma unroll
-    for (int msk = 1; msk <= 8; msk <<= 1)
-#pragma unroll
-      for (int b = 0; b < KRB; b++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const float om = shfl_xor(m[b][i], msk);
-          const float oz = shfl_xor(z[b][i], msk);
-          const float M = fmaxf(m[b][i], om);
-          float zz = 0.f;
-          if (z[b][i] > 0.f) zz += z[b][i] * fast_exp2(m[b][i] - M);
-          if (oz > 0.f) zz += oz * fast_exp2(om - M);
-          m[b][i] = M;
-          z[b][i] = zz;
-        }
-#pragma unroll
-    for (int b = 0; b < KRB; b++)
-#pragma unroll
-      for (int i = 0; i < 4; i++) z[b][i] = z[b][i] > 0.f ? 1.0f / z[b][i] : 0.f;  // now 1 / normaliser
-    // Pass 2: probabilities, column sums into the LDS accumulator.
-    stream([&](const u32x4 (&kv)[WGeo<D>::NV], int key0) {
-      if (!active) return;
-      float4_t cc[KRB];
-      logits_tile_n<D, KRB>(qa, kv, cc);
-      const int j = key0 + col;
-      float cs = 0.f;
-#pragma unroll
-      for (int b = 0; b < KRB; b++)
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-          if (j < nr[b][i] && z[b][i] > 0.f) cs += fast_exp2(cc[b][i] * c - m[b][i]) * z[b][i];
-      cs += shfl_xor(cs, 16);
-      cs += shfl_xor(cs, 32);
-      if (gq == 0 && j < n) fix_add(&acc[j], cs);
-    });
+  const Window<D> w{p, lds, make_rsrc(Q, (uint32_t)R * D * 2u), make_rsrc(K, (uint32_t)n * D * 2u), n, R,
+                    __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), (int)(threadIdx.x % kWave),
+                    p.scale * kLog2e, p.scores + (size_t)unit * p.cap};
+  const int slots = ((n + 15) / 16 + kNW - 1) / kNW;  // 16-key tiles per wave
+  bool done = false;
+  if (slots <= 2) done = w.fresh().template one_pass<2, 2>();
+  else if (slots <= 4) done = w.fresh().template one_pass<4, 4>();
+  else if (slots <= kKeyTiles) {
+    // The causal mask reaches the last two tiles of a wave only, or all.
+    if (n >= p.nq && (n - p.nq + 1) / (16 * kNW) >= kKeyTiles - 2) done = w.fresh().template one_pass<6, 2>();
+    else done = w.fresh().template one_pass<6, 6>();
   }
-  __syncthreads();
-  float *sc = p.scores + (size_t)unit * p.cap;
-  for (int j = tid; j < n; j += NW * kWave) sc[j] = p.accumulate ? sc[j] + fix_value(acc[j]) : fix_value(acc[j]);
+  if (!done) w.two_pass(slots);
 }
 
 }  // namespace
-
-size_t window_scores_tiled_lds_bytes(int cap, int D) {
-  return ((size_t)((cap + 1) & ~1)) * sizeof(unsigned long long) + 2 * (size_t)kTK * D * 2;
-}
 
 hipError_t launch_accumulate_scores(const ScoreParams &p, hipStream_t stream) {
   const dim3 grid(p.S * p.L * p.Hkv);
@@ -519,17 +557,8 @@ hipError_t launch_accumulate_scores(const ScoreParams &p, hipStream_t stream) {
     const size_t lds = ((size_t)p.D + 2 * (size_t)p.cap) * sizeof(float);
     hipLaunchKernelGGL(window_scores_kernel<float>, grid, dim3(64), lds, stream, p);
   } else {
-    const size_t tiled = window_scores_tiled_lds_bytes(p.cap, p.D);
-    if (tiled <= 65536) {
-      if (p.D == 128) hipLaunchKernelGGL((window_scores_tiled<128, 8, 2>), grid, dim3(512), tiled, stream, p);
-      else hipLaunchKernelGGL((window_scores_tiled<64, 8, 2>), grid, dim3(512), tiled, stream, p);
-    } else {
-      // Caches too long for the ring beside the accumulator: one wave streams
-      // K per two row blocks (more K traffic, same result).
-      const size_t lds = (size_t)p.cap * sizeof(unsigned long long);
-      if (p.D == 128) hipLaunchKernelGGL(window_scores_bf16<128>, grid, dim3(256), lds, stream, p);
-      else hipLaunchKernelGGL(window_scores_bf16<64>, grid, dim3(256), lds, stream, p);
-    }
+    if (p.D == 128) hipLaunchKernelGGL(window_scores_bf16<128>, grid, dim3(kNW * kWave), 0, stream, p);
+    else hipLaunchKernelGGL(window_scores_bf16<64>, grid, dim3(kNW * kWave), 0, stream, p);
   }
   return hipGetLastError();
 }

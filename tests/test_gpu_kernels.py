@@ -408,6 +408,54 @@ def test_accumulate_scores(dt, D, G, nq, cap):
         assert torch.equal(again.view(torch.int32), first.view(torch.int32))
 
 
+@pytest.mark.parametrize("D,G,nq,lens,std,shift", [
+    # One pass: one, two, four and six 16-key tiles per wave, the mask inside the last two or all.
+    (128, 7, 32, [1, 127, 128, 129, 255, 256, 257], 1.0, 0.0),
+    (128, 7, 128, [511, 512, 513, 640, 700, 767, 768], 1.0, 0.0),
+    (64, 4, 9, [16, 33, 300, 500, 513, 768], 1.0, 0.0),
+    (128, 4, 300, [200, 299, 400, 768], 1.0, 0.0),       # more window rows than keys; the mask in every tile
+    # Two passes: row groups of 896 (one, and two of 512), tiles per wave 1 .. 7, key slots 7 .. 9.
+    (128, 7, 128, [769, 832, 897, 1100], 1.0, 0.0),
+    (128, 8, 128, [770, 1025], 1.0, 0.0),
+    (64, 3, 100, [769, 1000], 1.0, 0.0),
+    (128, 1, 1, [1, 769, 1100], 1.0, 0.0),
+    # Logits outside the reference-free range: wide ones, and rows shifted far up or down as a whole.
+    (128, 7, 32, [40, 300, 700], 12.0, 0.0),
+    (128, 2, 20, [40, 300, 700, 900], 1.0, 6.0),
+    (64, 8, 128, [130, 768, 1000], 1.0, 8.0),
+])
+def test_accumulate_scores_edges(D, G, nq, lens, std, shift):
+    """Window scores at the edges of the tiles, waves and row groups, and with
+    logits beyond the range in which a row needs no reference. A logit's float32
+    sum is off by about 2^-24 of its largest terms, so its probability's
+    relative error, and the score's, grows with the logits' size: 1e-4 at unit
+    scale (as above), times the factor by which the logits are larger."""
+    k = kvr()
+    S, L, Hkv, cap = len(lens), 1, 2, max(lens) + 3
+    g = torch.Generator().manual_seed(D + G + nq + len(lens))
+    K = (torch.randn((S, L, Hkv, cap, D), generator=g) + shift * torch.randn((S, L, Hkv, 1, D), generator=g)).to(torch.bfloat16)
+    V = randn((S, L, Hkv, cap, D), g, torch.bfloat16)
+    qw = randn((S, L, Hkv * G, nq, D), g, torch.bfloat16, std)
+    scale = 1.0 / math.sqrt(D)
+    cache = k.Cache(K.to(DEV), V.to(DEV), None)
+    for s, n in enumerate(lens):
+        cache.k[s, :, :, n:] = float("nan")  # slots past the live end are never read
+    lent = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    sc = torch.full((S, L, Hkv, cap), 0.25, device=DEV)
+    say("window score edges", D, G, nq, lens, std, shift)
+    k.accumulate_scores(cache, lent, qw.to(DEV), scale, sc, accumulate=False)
+    torch.cuda.synchronize()
+    ref = oracle.window_scores(host(K), host(V), np.array(lens), host(qw), scale)
+    got = sc.cpu().double().numpy()
+    for s, n in enumerate(lens):
+        assert np.abs(got[s, ..., :n] - ref[s, ..., :n]).max() <= 1e-4 * max(1.0, std, shift)
+        assert (got[s, ..., n:] == 0.25).all()
+    again = torch.full((S, L, Hkv, cap), 0.25, device=DEV)
+    k.accumulate_scores(cache, lent, qw.to(DEV), scale, again, accumulate=False)
+    torch.cuda.synchronize()
+    assert torch.equal(again.view(torch.int32), sc.view(torch.int32))
+
+
 # ------------------------------------------------------------ entropy
 
 ENT_CASES = [
