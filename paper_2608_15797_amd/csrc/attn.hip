@@ -33,7 +33,7 @@
 // finish in one round. The private suffix then runs as its own unit per
 // (candidate, layer, KV head) and folds those partials in by log-sum-exp.
 //
-// f32 path: plain VALU kernel (one wave per unit) for float32 caches.
+// f32 path: VALU kernel (one workgroup per unit) for float32 caches.
 //
 // This file is compiled twice. With KVR_ATTN_WIDE = 1 (attn_wide.hip) it
 // provides only the context kernels of three and four row blocks
@@ -1039,17 +1039,41 @@ __global__ __launch_bounds__(64) void attn_prefix_rows_bf16(AttnParams p, Entrop
 
 #if !KVR_ATTN_WIDE
 // ---------------------------------------------------------------------------
-// float32 path: one wave per (sequence, layer, KV head), VALU arithmetic.
-// LDS: q rows [G][D], logits [G][nt_max], stats [2][16].
-__global__ __launch_bounds__(64) void attn_f32(AttnParams p, int nt_max) {
-  extern __shared__ float smem[];
+// float32 path: one workgroup of four waves per (sequence, layer, KV head),
+// VALU arithmetic. Bound by the caches' bytes, so every row is read once, in
+// whole 128-byte lines, whatever G is:
+//   * logits: a key row is read by 8 lanes of D/8 elements, 8 rows per load
+//     instruction and 32 rows per wave at a time; each of the G dot products
+//     is then D/8 fused multiply-adds per lane (the query slice comes from
+//     LDS, one read for four rows) and three DPP additions;
+//   * softmax: a wave per head, over the logits in LDS, one exp per logit;
+//   * output: a value row is read by D/4 lanes, 4 rows at a time per group of
+//     lanes, and added to the G heads' sums in registers (GM >= G of them);
+//     the groups' sums meet in LDS.
+// One wave per unit with a key per lane (whole rows strided over the lanes,
+// read again for every head) took 1640 us for 8 x 28 x 4 units of 129-257
+// tokens (G = 7, D = 128); this takes 46 us
+// (184 MB, 4.0 TB/s).
+// LDS: q rows [G][D], logits [G][ld], stats [2][16]; the groups' sums
+// [4][G][D] over the first two once they are used.
+constexpr int kF32Threads = 256;
+
+template <int CTRL>
+__device__ __forceinline__ float add_dpp(float v) {
+  return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+template <int D, int GM>
+__global__ __launch_bounds__(kF32Threads) void attn_f32(AttnParams p, int ld, int lds_stat) {
+  extern __shared__ __align__(16) float smem[];
+  constexpr int NW = kF32Threads / kWave;
   const int unit = blockIdx.x;
   const int h = unit % p.Hkv;
   const int sl = unit / p.Hkv;
   const int l = sl % p.L;
   const int s = sl / p.L;
-  const int lane = threadIdx.x;
-  const int G = p.G, D = p.D;
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int G = p.G;
   int n = p.len[s];
   n = n < 0 ? 0 : (n > p.cap ? p.cap : n);
   const int npre = p.P > 0 ? p.plen : 0;
@@ -1067,66 +1091,139 @@ __global__ __launch_bounds__(64) void attn_f32(AttnParams p, int nt_max) {
     Vp = static_cast<const float *>(p.pv) + pbase;
   }
   if (kn && n >= 1) {
-    for (int d = lane; d < D; d += kWave) {
+    for (int d = tid; d < D; d += kF32Threads) {
       Kc[(size_t)(n - 1) * D + d] = kn[d];
       Vc[(size_t)(n - 1) * D + d] = vn[d];
     }
-    if (lane == 0 && p.pos && p.new_pos) p.pos[(size_t)unit * p.cap + n - 1] = p.new_pos[s];
+    if (tid == 0 && p.pos && p.new_pos) p.pos[(size_t)unit * p.cap + n - 1] = p.new_pos[s];
   }
-  auto krow = [&](int j) -> const float * {
-    if (j < npre) return Kp + (size_t)j * D;
+  // Row j of the context, then the cache, whose last row is the new token's.
+  auto row = [&](const float *pre, const float *own, const float *last, int j) -> const float * {
     const int js = j - npre;
-    return (kn && js == n - 1) ? kn : Kc + (size_t)js * D;
-  };
-  auto vrow = [&](int j) -> const float * {
-    if (j < npre) return Vp + (size_t)j * D;
-    const int js = j - npre;
-    return (vn && js == n - 1) ? vn : Vc + (size_t)js * D;
+    const float *r = j < npre ? pre + (size_t)j * D : own + (size_t)js * D;
+    return last && js == n - 1 ? last : r;
   };
   float *qs = smem;
   float *xs = smem + G * D;
-  float *stat = xs + (size_t)G * nt_max;
+  float *stat = smem + lds_stat;
   const size_t qrow0 = ((size_t)s * p.L + l) * p.Hq + h * G;
-  for (int e = lane; e < G * D; e += kWave) qs[e] = static_cast<const float *>(p.q)[qrow0 * D + e];
+  for (int e = tid; e < G * D; e += kF32Threads) qs[e] = static_cast<const float *>(p.q)[qrow0 * D + e];
   __syncthreads();
-  for (int g = 0; g < G; g++) {
-    float mloc = kNegInf;
+
+  // Logits. Lane part of 8 holds floats 4 part + 32 i of rows base + 8 b + sub.
+  constexpr int NV = D / 32, NB = 4;
+  const int part = lane % 8, sub = lane / 8;
+  for (int base = wave * 8 * NB; base < nt; base += NW * 8 * NB) {
+    float4_t kv[NB][NV];
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+      const int j = base + 8 * b + sub;
+      const float *r = row(Kp, Kc, kn, j < nt ? j : nt - 1) + 4 * part;
+#pragma unroll
+      for (int i = 0; i < NV; i++) kv[b][i] = *reinterpret_cast<const float4_t *>(r + 32 * i);
+    }
+    for (int g = 0; g < G; g++) {
+      float dot[NB] = {};
+#pragma unroll
+      for (int i = 0; i < NV; i++) {
+        const float4_t q = *reinterpret_cast<const float4_t *>(qs + g * D + 32 * i + 4 * part);
+#pragma unroll
+        for (int b = 0; b < NB; b++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) dot[b] = fmaf(q[e], kv[b][i][e], dot[b]);
+      }
+      float x = 0.f;
+#pragma unroll
+      for (int b = 0; b < NB; b++) {
+        float v = add_dpp<0xB1>(dot[b]);  // swap neighbours, swap pairs, mirror the 8 lanes
+        v = add_dpp<0x4E>(v);
+        v = add_dpp<0x141>(v);
+        x = part == b ? v : x;
+      }
+      const int j = base + 8 * part + sub;
+      if (part < NB && j < nt) xs[g * ld + j] = x * p.scale;
+    }
+  }
+  __syncthreads();
+
+  // Softmax numerators in place; 1 / sum of each head in stat.
+  for (int g = wave; g < G; g += NW) {
+    float m = kNegInf;
+    for (int j = lane; j < nt; j += kWave) m = fmaxf(m, xs[g * ld + j]);
+    m = wave_max(m);
+    float z = 0.f;
     for (int j = lane; j < nt; j += kWave) {
-      const float *kr = krow(j);
-      float dot = 0.f;
-      for (int d = 0; d < D; d++) dot = fmaf(qs[g * D + d], kr[d], dot);
-      const float x = dot * p.scale;
-      xs[g * nt_max + j] = x;
-      mloc = fmaxf(mloc, x);
+      const float e = expf(xs[g * ld + j] - m);
+      xs[g * ld + j] = e;
+      z += e;
     }
-    const float m = wave_max(mloc);
-    float zloc = 0.f;
-    for (int j = lane; j < nt; j += kWave) zloc += expf(xs[g * nt_max + j] - m);
-    const float z = wave_sum(zloc);
-    if (lane == 0) { stat[g] = m; stat[16 + g] = 1.0f / z; }
+    z = wave_sum(z);
+    if (lane == 0) stat[g] = nt > 0 ? 1.0f / z : 0.f;
   }
   __syncthreads();
-  float *out = static_cast<float *>(p.out);
-  for (int g = 0; g < G; g++) {
-    const float m = stat[g], iz = stat[16 + g];
-    for (int d = lane; d < D; d += kWave) {
-      float acc = 0.f;
-      for (int j = 0; j < nt; j++) acc = fmaf(expf(xs[g * nt_max + j] - m) * iz, vrow(j)[d], acc);
-      out[(qrow0 + g) * D + d] = acc;
-    }
-  }
+
+  // Window score of the step, as in the bf16 kernel.
   const int wstart = p.B + p.buffer + 2 - p.W;
   if (p.scores != nullptr && p.P == 0 && n >= wstart) {
     const bool first = n == wstart;
     float *sc = p.scores + (size_t)unit * p.cap;
-    for (int j = lane; j < n; j += kWave) {
+    for (int j = tid; j < n; j += kF32Threads) {
       float r = 0.f;
-      for (int g = 0; g < G; g++) r += expf(xs[g * nt_max + j] - stat[g]) * stat[16 + g];
-      if (first || j == n - 1)
-        sc[j] = r;
-      else
-        sc[j] += r;
+      for (int g = 0; g < G; g++) r += xs[g * ld + j] * stat[g];
+      sc[j] = (first || j == n - 1) ? r : sc[j] + r;
     }
+  }
+
+  // Output sums: group `slot` of LPR lanes takes keys 4 slot + i + 4 SL * it.
+  constexpr int LPR = D / 4, SL = kF32Threads / LPR;
+  const int slot = tid / LPR, d0 = 4 * (tid % LPR);
+  const bool wide = ld % 4 == 0;
+  float4_t acc[GM];
+#pragma unroll
+  for (int g = 0; g < GM; g++) acc[g] = float4_t{0.f, 0.f, 0.f, 0.f};
+  for (int j0 = 4 * slot; j0 < nt; j0 += 4 * SL) {
+    float4_t vv[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int j = j0 + i;
+      vv[i] = *reinterpret_cast<const float4_t *>(row(Vp, Vc, vn, j < nt ? j : nt - 1) + d0);
+      if (j >= nt) vv[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int g = 0; g < GM; g++)
+      if (g < G) {
+        const float *x = xs + g * ld + j0;
+        float4_t e;
+        if (wide) {
+          e = *reinterpret_cast<const float4_t *>(x);  // slots past nt: not used
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; i++) e[i] = j0 + i < nt ? x[i] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++) acc[g] += (j0 + i < nt ? e[i] : 0.f) * vv[i];
+      }
+  }
+  // The groups of a wave by shuffles, the waves through LDS.
+#pragma unroll
+  for (int g = 0; g < GM; g++)
+    if (g < G)
+#pragma unroll
+      for (int msk = LPR; msk < kWave; msk <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; e++) acc[g][e] += shfl_xor(acc[g][e], msk);
+  __syncthreads();  // the logits are used
+  if (lane < LPR)
+#pragma unroll
+    for (int g = 0; g < GM; g++)
+      if (g < G) *reinterpret_cast<float4_t *>(smem + (wave * G + g) * D + d0) = acc[g];
+  __syncthreads();
+  float *out = static_cast<float *>(p.out) + qrow0 * D;
+  for (int e = tid; e < G * D; e += kF32Threads) {
+    float v = smem[e];
+#pragma unroll
+    for (int w = 1; w < NW; w++) v += smem[w * G * D + e];
+    out[e] = v * stat[e / D];
   }
 }
 #endif  // !KVR_ATTN_WIDE
@@ -1223,6 +1320,25 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
   return hipGetLastError();
 }
 
+#if !KVR_ATTN_WIDE
+template <int D>
+void launch_f32(const AttnParams &p, hipStream_t stream) {
+  // Logit rows of nt tokens, padded to 16 bytes (one read for four tokens)
+  // where the padding still fits in the LDS that the arguments were checked
+  // against; the waves' output sums take the place of queries and logits.
+  const size_t nt = (size_t)(p.P > 0 ? p.plen : 0) + p.cap;
+  size_t ld = (nt + 3) / 4 * 4;
+  if ((p.G * (D + ld) + 32) * sizeof(float) > kMaxLds) ld = nt;
+  size_t stat = p.G * (D + ld);
+  if (stat < (size_t)4 * p.G * D) stat = (size_t)4 * p.G * D;
+  const size_t lds = (stat + 32) * sizeof(float);
+  const dim3 grid(p.S * p.L * p.Hkv);
+  if (p.G <= 4) hipLaunchKernelGGL((attn_f32<D, 4>), grid, dim3(kF32Threads), lds, stream, p, (int)ld, (int)stat);
+  else if (p.G <= 8) hipLaunchKernelGGL((attn_f32<D, 8>), grid, dim3(kF32Threads), lds, stream, p, (int)ld, (int)stat);
+  else hipLaunchKernelGGL((attn_f32<D, 16>), grid, dim3(kF32Threads), lds, stream, p, (int)ld, (int)stat);
+}
+#endif  // !KVR_ATTN_WIDE
+
 // Whole logit rows, one wave per row, as a kernel of its own (the entropy
 // rows of a float32-cache launch, whose attention kernel has no such lanes).
 template <typename T, bool SAMPLE>
@@ -1237,12 +1353,6 @@ __global__ __launch_bounds__(64) void entropy_rows_kernel(EntropyBatch e) {
 }
 
 }  // namespace
-
-#if !KVR_ATTN_WIDE
-size_t f32_attn_lds_bytes(int G, int D, int plen, int cap) {
-  return ((size_t)G * D + (size_t)G * (plen + cap) + 32) * sizeof(float);
-}
-#endif
 
 namespace {
 
@@ -1324,9 +1434,8 @@ size_t attn_workspace_bytes(int S, int L, int Hq, int D, int nsplit) {
 
 hipError_t launch_decode_attn(const AttnParams &p, const EntropyBatch *ent, hipStream_t stream) {
   if (p.dtype == 0) {
-    const int nt_max = (p.P > 0 ? p.plen : 0) + p.cap;
-    const size_t lds = f32_attn_lds_bytes(p.G, p.D, p.P > 0 ? p.plen : 0, p.cap);
-    hipLaunchKernelGGL(attn_f32, dim3(p.S * p.L * p.Hkv), dim3(64), lds, stream, p, nt_max);
+    if (p.D == 128) launch_f32<128>(p, stream);
+    else launch_f32<64>(p, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !ent) return e;
     const dim3 rows(ent->row0[ent->nsets]);

@@ -216,6 +216,26 @@ def test_decode_attn_prefix(case):
     assert err.max() <= TOL[dt]
 
 
+# float32 caches: every group size class (4, 8, 16 heads), lengths around the 32 rows of a wave, LDS at its limit
+# with and without room for padded logit rows.
+@pytest.mark.parametrize("case", [
+    (3, 1, 2, 1, 128, 20, 5, 11, torch.float32), (3, 2, 2, 3, 64, 40, 8, 88, torch.float32),
+    (3, 1, 2, 5, 128, 100, 32, 32, torch.float32), (2, 1, 1, 9, 64, 20, 5, 11, torch.float32),
+    (2, 1, 1, 16, 64, 700, 64, 256, torch.float32), (2, 1, 1, 16, 128, 700, 64, 190, torch.float32),
+    (2, 1, 2, 7, 128, 1950, 64, 255, torch.float32),
+], ids=lambda c: "G%dD%d_B%d" % (c[3], c[4], c[5]))
+def test_decode_attn_f32_shapes(case):
+    test_decode_attn_base_with_scores(case)
+
+
+@pytest.mark.parametrize("case", [
+    (4, 2, 1, 2, 6, 128, 1000, 40, torch.float32), (4, 1, 2, 1, 12, 64, 33, 17, torch.float32),
+    (2, 2, 1, 2, 16, 64, 930, 27, torch.float32),
+], ids=lambda c: "G%dD%d_plen%d" % (c[4], c[5], c[6]))
+def test_decode_attn_prefix_f32_shapes(case):
+    test_decode_attn_prefix(case)
+
+
 def test_prefix_workspace_errors():
     k = kvr()
     cache = k.Cache.empty(4, 1, 2, 8, 128, torch.bfloat16, DEV, with_pos=False)
