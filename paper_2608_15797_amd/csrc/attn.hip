@@ -1081,8 +1081,9 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32(AttnParams p, int ld, in
   const size_t ubase = (size_t)unit * p.cap * D;
   float *Kc = static_cast<float *>(p.k) + ubase;
   float *Vc = static_cast<float *>(p.v) + ubase;
-  const float *kn = p.k_new ? static_cast<const float *>(p.k_new) + (size_t)unit * D : nullptr;
-  const float *vn = p.v_new ? static_cast<const float *>(p.v_new) + (size_t)unit * D : nullptr;
+  // The new token's rows; none without a live slot to append to (n = 0).
+  const float *kn = p.k_new && n >= 1 ? static_cast<const float *>(p.k_new) + (size_t)unit * D : nullptr;
+  const float *vn = p.v_new && n >= 1 ? static_cast<const float *>(p.v_new) + (size_t)unit * D : nullptr;
   const float *Kp = nullptr, *Vp = nullptr;
   if (p.P > 0) {
     const int pp = s / p.C;
@@ -1090,7 +1091,7 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32(AttnParams p, int ld, in
     Kp = static_cast<const float *>(p.pk) + pbase;
     Vp = static_cast<const float *>(p.pv) + pbase;
   }
-  if (kn && n >= 1) {
+  if (kn) {
     for (int d = tid; d < D; d += kF32Threads) {
       Kc[(size_t)(n - 1) * D + d] = kn[d];
       Vc[(size_t)(n - 1) * D + d] = vn[d];

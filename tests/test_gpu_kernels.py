@@ -236,6 +236,32 @@ def test_decode_attn_prefix_f32_shapes(case):
     test_decode_attn_prefix(case)
 
 
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+def test_decode_attn_prefix_empty_suffix(dt):
+    """A sequence without live slots (len 0) attends to its context alone: the
+    new token's rows are neither read nor stored."""
+    k = kvr()
+    S, L, Hkv, G, D, plen, scap = 3, 1, 2, 2, 128, 70, 9
+    say("empty suffix", dt)
+    g = torch.Generator().manual_seed(5)
+    PK, PV = randn((S, L, Hkv, plen, D), g, dt), randn((S, L, Hkv, plen, D), g, dt)
+    K, V = randn((S, L, Hkv, scap, D), g, dt), randn((S, L, Hkv, scap, D), g, dt)
+    q = randn((S, L, Hkv * G, D), g, dt)
+    kn, vn = randn((S, L, Hkv, D), g, dt), randn((S, L, Hkv, D), g, dt)
+    cache, prefix = k.Cache(K.to(DEV), V.to(DEV), None), k.Prefix(PK.to(DEV), PV.to(DEV))
+    nws = k.decode_attn_workspace_size(cache, prefix, Hkv * G)
+    ws = torch.zeros(max(nws, 16) // 4, dtype=torch.float32, device=DEV)
+    out = torch.empty((S, L, Hkv * G, D), dtype=dt, device=DEV)
+    lens = torch.zeros(S, dtype=torch.int32, device=DEV)
+    k.decode_attn(cache, lens, q.to(DEV), out, 1.0 / math.sqrt(D), k_new=kn.to(DEV), v_new=vn.to(DEV), prefix=prefix,
+                  workspace=ws)
+    torch.cuda.synchronize()
+    x = (q.double().view(S, L, Hkv, G, D) @ PK.double().transpose(-1, -2)) / math.sqrt(D)
+    ref = (torch.softmax(x, -1) @ PV.double()).view(S, L, Hkv * G, D).numpy()
+    assert rowwise_rel_err(as_f64(out), ref).max() <= TOL[dt]
+    assert torch.equal(cache.k.cpu(), K) and torch.equal(cache.v.cpu(), V)
+
+
 def test_prefix_workspace_errors():
     k = kvr()
     cache = k.Cache.empty(4, 1, 2, 8, 128, torch.bfloat16, DEV, with_pos=False)
