@@ -107,11 +107,15 @@ constexpr float kSlack = 8.0f;
 
 __device__ __forceinline__ float vmax(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 
-// Fold eight raw logits x into the triple, y = c * x with c > 0.
-__device__ __forceinline__ void tri_fold8(Tri &t, const float (&x)[8], float c) {
-  // NaN-propagating maximum: no operand canonicalisation, three-input
-  // instructions (NaN logits are unsupported anyway).
-  const float lm = vmax(vmax(vmax(x[0], x[1]), vmax(x[2], x[3])), vmax(vmax(x[4], x[5]), vmax(x[6], x[7]))) * c;
+// Largest of eight raw logits: NaN-propagating maximum, no operand
+// canonicalisation, three-input instructions (NaN logits are unsupported anyway).
+__device__ __forceinline__ float max8(const float (&x)[8]) {
+  return vmax(vmax(vmax(x[0], x[1]), vmax(x[2], x[3])), vmax(vmax(x[4], x[5]), vmax(x[6], x[7])));
+}
+
+// Fold eight raw logits x (xm: their largest) into the triple, y = c * x with c > 0.
+__device__ __forceinline__ void tri_fold8(Tri &t, const float (&x)[8], float xm, float c) {
+  const float lm = xm * c;
   if (lm > t.m + kSlack) {
     if (t.z > 0.f) {
       const float f = fast_exp2(t.m - lm);
@@ -130,6 +134,8 @@ __device__ __forceinline__ void tri_fold8(Tri &t, const float (&x)[8], float c) 
     t.s = fmaf(d, w, t.s);
   }
 }
+
+__device__ __forceinline__ void tri_fold8(Tri &t, const float (&x)[8], float c) { tri_fold8(t, x, max8(x), c); }
 
 __device__ __forceinline__ float load1(const bf16_t *ptr) { return bf16_to_f32(*ptr); }
 __device__ __forceinline__ float load1(const float *ptr) { return *ptr; }
@@ -170,56 +176,100 @@ __device__ __forceinline__ int batch_set(const EntropyBatch &b, int g) {
   return k;
 }
 
-// Entropy (and detector update) of one whole logit row by one 64-lane wave:
-// the row streams through two banks of U 16-byte vector loads per lane (the
-// next bank's loads are in flight while the current one is folded), lanes
-// take consecutive vectors so every load instruction reads 1 KiB, and the
-// row's triple is reduced across the wave with shuffles. No partials leave
-// the wave. The row must start 16-byte aligned.
+// The lanes' triples merged across the wave.
+__device__ __forceinline__ Tri wave_merge(Tri t) {
+#pragma unroll
+  for (int msk = 32; msk >= 1; msk >>= 1) {
+    Tri o{shfl_xor(t.m, msk), shfl_xor(t.z, msk), shfl_xor(t.s, msk)};
+    t = tri_merge(t, o);
+  }
+  return t;
+}
+
+// The triple of the vectors [v0, v1) of 8 logits of a row by one 64-lane wave
+// (with the row's V % 8 trailing logits if `last`): they stream through two
+// banks of U 16-byte vector loads per lane (the next bank's loads are in
+// flight while the current one is folded), lanes take consecutive vectors so
+// every load instruction reads 1 KiB, and the triple is reduced across the
+// wave with shuffles. mx: the lane's largest logit (its value before, if that
+// is larger). The row must start 16-byte aligned.
 template <typename T, int U>
-__device__ __forceinline__ void entropy_row_wave(const EntropyParams &p, int row, int lane) {
+__device__ __forceinline__ Tri entropy_fold_wave(const EntropyParams &p, int row, int lane, int v0, int v1, bool last,
+                                                 float &mx) {
   const T *x = static_cast<const T *>(p.logits) + (size_t)row * p.ld;
   const float c = p.inv_temp * kLog2e;
-  const int nvec = p.V / 8;
-  const rsrc_t rr = row_rsrc(x, (uint32_t)nvec * 8u * (uint32_t)sizeof(T));
+  const rsrc_t rr = row_rsrc(x, (uint32_t)v1 * 8u * (uint32_t)sizeof(T));
   constexpr int BANK = U * kWave;  // vectors per bank
   Tri t{kNegInf, 0.f, 0.f};
+  auto fold = [&](const float (&y)[8]) {
+    const float xm = max8(y);
+    mx = vmax(mx, xm);
+    tri_fold8(t, y, xm, c);
+  };
   Vec8<T> a[U], b[U];
 #pragma unroll
-  for (int u = 0; u < U; u++) a[u].load(rr, u * kWave + lane);
-  for (int v0 = 0; v0 < nvec; v0 += 2 * BANK) {
+  for (int u = 0; u < U; u++) a[u].load(rr, v0 + u * kWave + lane);
+  for (; v0 < v1; v0 += 2 * BANK) {
 #pragma unroll
     for (int u = 0; u < U; u++) b[u].load(rr, v0 + BANK + u * kWave + lane);
 #pragma unroll
     for (int u = 0; u < U; u++) {
       float y[8];
       a[u].get(y);
-      if (v0 + u * kWave + lane < nvec) tri_fold8(t, y, c);
+      if (v0 + u * kWave + lane < v1) fold(y);
     }
-    if (v0 + BANK >= nvec) break;
+    if (v0 + BANK >= v1) break;
 #pragma unroll
     for (int u = 0; u < U; u++) a[u].load(rr, v0 + 2 * BANK + u * kWave + lane);
 #pragma unroll
     for (int u = 0; u < U; u++) {
       float y[8];
       b[u].get(y);
-      if (v0 + BANK + u * kWave + lane < nvec) tri_fold8(t, y, c);
+      if (v0 + BANK + u * kWave + lane < v1) fold(y);
     }
   }
-  // The V % 8 trailing logits, one per lane.
-  const int e = nvec * 8 + lane;
-  if (e < p.V) {
-    float y[1] = {load1(x + e) * c};
+  const int e = p.V / 8 * 8 + lane;
+  if (last && e < p.V) {
+    const float xe = load1(x + e);
+    float y[1] = {xe * c};
+    mx = vmax(mx, xe);
     tri_add<1>(t, y);
   }
-#pragma unroll
-  for (int msk = 32; msk >= 1; msk >>= 1) {
-    Tri o{shfl_xor(t.m, msk), shfl_xor(t.z, msk), shfl_xor(t.s, msk)};
-    t = tri_merge(t, o);
-  }
+  return wave_merge(t);
+}
+
+// Entropy and detector update of a row from its triple, by one wave.
+__device__ __forceinline__ void entropy_put(const EntropyParams &p, int row, int lane, Tri t) {
   const float H = finish_entropy(t);
   if (lane == 0) p.H[row] = H;
   detector_push(p, row, H, lane);
+}
+
+// Entropy (and detector update) of one whole logit row by one wave. No
+// partials leave the wave.
+template <typename T, int U>
+__device__ __forceinline__ void entropy_row_wave(const EntropyParams &p, int row, int lane) {
+  float mx = kNegInf;
+  entropy_put(p, row, lane, entropy_fold_wave<T, U>(p, row, lane, 0, p.V / 8, true, mx));
+}
+
+// The same by a workgroup of NW waves (one wave's row is a chain of its
+// banks, about 25 us for 152064 logits, which a launch of few attention units
+// would wait for): a share of the vectors each, the triples merged by the
+// first. part: NW triples of LDS.
+template <typename T, int U, int NW>
+__device__ __forceinline__ void entropy_row_group(const EntropyParams &p, int row, int lane, int wave, Tri *part) {
+  const int nvec = p.V / 8, per = (nvec + NW - 1) / NW;
+  const int v0 = min(wave * per, nvec), v1 = min(v0 + per, nvec);
+  float mx = kNegInf;
+  Tri t = entropy_fold_wave<T, U>(p, row, lane, v0, v1, wave == NW - 1, mx);
+  if (lane == 0) part[wave] = t;
+  __syncthreads();
+  if (wave != 0) return;
+  t = part[0];
+#pragma unroll
+  for (int w = 1; w < NW; w++) t = tri_merge(t, part[w]);
+  entropy_put(p, row, lane, t);
 }
 
 }  // namespace

@@ -179,21 +179,17 @@ __device__ __forceinline__ uint64_t philox_w0(uint64_t c0, uint64_t c1, uint64_t
   return c0;
 }
 
-// The draw of one row by one wave from its k best candidate keys win[0 ..
-// nwin) (unordered; nwin <= kTopKMax, 0 = empty): keys sorted descending by
-// rank counting into `sorted`, the temperature softmax over them relative to
-// the largest, the shortest prefix reaching top_p of the mass, and the
-// inverse-CDF draw with u = top 24 bits of Philox4x64-10 at counter (step,
-// row, 0, 0), key (seed, 0). Writes p.tokens[row].
-__device__ __forceinline__ void sample_draw(const EntropyParams &p, int row, int lane, uint64_t *win,
-                                            uint64_t *sorted, int nwin) {
-  wave_lds_sync();
-  const uint64_t key = lane < nwin ? win[lane] : 0;
-  int rank = 0;
-  for (int j = 0; j < nwin; j++) rank += win[j] > key;
-  if (lane < nwin) sorted[rank] = key;
-  wave_lds_sync();
-  const uint64_t mine = lane < nwin ? sorted[lane] : 0;
+// The uniform of a row's draw: top 24 bits of Philox4x64-10 at counter (step,
+// row, 0, 0), key (seed, 0).
+__device__ __forceinline__ float row_uniform(const EntropyParams &p, int row) {
+  return (float)(philox_w0(p.step, (uint64_t)row, p.seed, 0) >> 40) * (1.0f / 16777216.0f);
+}
+
+// The draw of one row by one wave from its k best candidate keys, sorted
+// descending over the lanes (0: none): the temperature softmax over them
+// relative to the largest, the shortest prefix reaching top_p of the mass, and
+// the inverse-CDF draw with the uniform u. Writes p.tokens[row].
+__device__ __forceinline__ void sample_pick(const EntropyParams &p, int row, int lane, uint64_t mine, float u) {
   const bool live = mine != 0;  // lanes 0 .. nwin - 1
   const float xr = live ? from_order_bits((uint32_t)(mine >> 32)) : kNegInf;
   const uint32_t id = ~(uint32_t)(mine & 0xffffffffu);
@@ -217,8 +213,6 @@ __device__ __forceinline__ void sample_draw(const EntropyParams &p, int row, int
     if (reach) keep = __ffsll((long long)reach);  // lowest lane + 1
   }
   const float mass = __shfl(cum, keep - 1, kWave);
-  const uint64_t w0 = philox_w0(p.step, (uint64_t)row, p.seed, 0);
-  const float u = (float)(w0 >> 40) * (1.0f / 16777216.0f);
   const float target = u * mass;
   const uint64_t over = __ballot(lane < keep && cum > target);
   const int pick = over ? __ffsll((long long)over) - 1 : keep - 1;
@@ -226,15 +220,112 @@ __device__ __forceinline__ void sample_draw(const EntropyParams &p, int row, int
   if (lane == 0) p.tokens[row] = (int32_t)tok;
 }
 
+// sample_pick from a row's k best keys win[0 .. nwin) in any order (nwin <=
+// kTopKMax, 0 = empty), sorted by rank counting into `sorted`.
+__device__ __forceinline__ void sample_draw(const EntropyParams &p, int row, int lane, uint64_t *win,
+                                            uint64_t *sorted, int nwin) {
+  wave_lds_sync();
+  const uint64_t key = lane < nwin ? win[lane] : 0;
+  int rank = 0;
+  for (int j = 0; j < nwin; j++) rank += win[j] > key;
+  if (lane < nwin) sorted[rank] = key;
+  wave_lds_sync();
+  sample_pick(p, row, lane, lane < nwin ? sorted[lane] : 0, row_uniform(p, row));
+}
+
 // Bytes of LDS a sampling row wave uses: its candidate buffer and the sorted
 // k best.
 constexpr size_t kSampleRowLds = (size_t)(kCandCap + kTopKMax) * sizeof(uint64_t);
 
+// The k best keys of the waves' candidate lists (wave w holds off[w+1]-off[w]
+// keys at cand[w * kCandCap ..]) stored unordered to out; returns how many.
+template <int NPL, int NW>
+__device__ __forceinline__ int gather_select(const uint64_t *cand, const int (&off)[NW + 1], int k, int lane,
+                                             uint64_t *out) {
+  uint64_t v[NPL];
+#pragma unroll
+  for (int i = 0; i < NPL; i++) {
+    const int j = lane + i * kWave;  // entry j of the concatenated lists
+    int w = 0;
+#pragma unroll
+    for (int q = 1; q < NW; q++) w += j >= off[q];
+    v[i] = j < off[NW] ? cand[w * kCandCap + (j - off[w])] : 0;
+  }
+  const uint64_t thr = select_threshold<NPL>(v, k, k);
+  return wave_store_ge<NPL>(out, v, thr, lane);
+}
+
+// A lower bound of the k-th best of a group's logits: the k-th largest of its
+// NW * 64 lanes' maxima (their order bits in LDS), to its 16 leading bits; -inf
+// if fewer than k are finite.
+template <int NW>
+__device__ __forceinline__ float group_bound(const uint32_t *lane_max, int lane, int k) {
+  uint32_t m[NW];
+#pragma unroll
+  for (int i = 0; i < NW; i++) m[i] = lane_max[lane + i * kWave];
+  uint32_t t = 0;
+  for (int b = 31; b >= 16; b--) {
+    const uint32_t cb = t | (1u << b);
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < NW; i++) n += __popcll(__ballot(m[i] >= cb));
+    if (n >= k) t = cb;
+  }
+  return t > order_bits(kNegInf) ? from_order_bits(t) : kNegInf;
+}
+
+// Offers the logits of the vectors [v0, v1) of a row (and of its tail if
+// `last`) to a wave's candidates. A second pass over a row that the entropy's
+// pass has just read: with the threshold from the lanes' maxima over the whole
+// row, all but about k vectors are passed over by one vote. A workgroup of four
+// waves takes 29 us for 152064 logits in the launch of a few attention units,
+// against 50 when its waves collect as one wave does below (17 for the entropy
+// alone).
+template <typename T, int U>
+__device__ __forceinline__ void offer_wave(const EntropyParams &p, int row, int lane, int v0, int v1, bool last,
+                                           Cands &cs) {
+  const T *x = static_cast<const T *>(p.logits) + (size_t)row * p.ld;
+  const rsrc_t rr = row_rsrc(x, (uint32_t)v1 * 8u * (uint32_t)sizeof(T));
+  constexpr int BANK = U * kWave;  // vectors per bank
+  Vec8<T> a[U], b[U];
+#pragma unroll
+  for (int u = 0; u < U; u++) a[u].load(rr, v0 + u * kWave + lane);
+  // Every lane offers in lockstep (vectors past the end offer nothing).
+  auto offer = [&](const Vec8<T> &w, int v) {
+    float y[8];
+    w.get(y);
+    const bool ok = v < v1;
+    if (__any(ok && max8(y) >= cs.vmin)) cand_offer(cs, p.top_k, lane, y, (uint32_t)v * 8u, ok ? 8 : 0);
+  };
+  for (; v0 < v1; v0 += 2 * BANK) {
+#pragma unroll
+    for (int u = 0; u < U; u++) b[u].load(rr, v0 + BANK + u * kWave + lane);
+#pragma unroll
+    for (int u = 0; u < U; u++) offer(a[u], v0 + u * kWave + lane);
+    if (v0 + BANK >= v1) break;
+#pragma unroll
+    for (int u = 0; u < U; u++) a[u].load(rr, v0 + 2 * BANK + u * kWave + lane);
+#pragma unroll
+    for (int u = 0; u < U; u++) offer(b[u], v0 + BANK + u * kWave + lane);
+  }
+  if (last) {
+    // The V % 8 trailing logits, one per lane.
+    const int e = p.V / 8 * 8 + lane;
+    float y[8] = {kNegInf, kNegInf, kNegInf, kNegInf, kNegInf, kNegInf, kNegInf, kNegInf};
+    const bool has = e < p.V;
+    if (has) y[0] = load1(x + e);
+    cand_offer(cs, p.top_k, lane, y, (uint32_t)e, has ? 1 : 0);
+  }
+  if (cs.cnt > p.top_k) cand_reduce_any(cs, p.top_k, p.top_k, lane);  // exactly the k best
+}
+
 // One whole logit row by one wave with the sampler: the entropy and detector
 // of entropy_row_wave, the row's k best logits collected into the wave's
 // candidate buffer as the row streams (thresholds seeded from the lane maxima
-// of the first bank), then the draw. Two banks of U vector loads, as there.
-// lds: kSampleRowLds bytes of LDS owned by the wave.
+// of the first bank), then the draw. Two banks of U vector loads, as there;
+// one pass, since beside a full chip's attention waves a second read of the
+// row costs more than the collecting saves (a launch of 7168 units 144 us
+// with it, 134 so). lds: kSampleRowLds bytes of LDS owned by the wave.
 template <typename T, int U>
 __device__ __forceinline__ void entropy_sample_row_wave(const EntropyParams &p, int row, int lane, uint64_t *lds) {
   const T *x = static_cast<const T *>(p.logits) + (size_t)row * p.ld;
@@ -253,9 +344,7 @@ __device__ __forceinline__ void entropy_sample_row_wave(const EntropyParams &p, 
     for (int u = 0; u < U; u++) {
       float y[8];
       a[u].get(y);
-      if (u * kWave + lane < nvec)
-#pragma unroll
-        for (int e = 0; e < 8; e++) mx = vmax(mx, y[e]);
+      if (u * kWave + lane < nvec) mx = vmax(mx, max8(y));
     }
     cand_seed(cs, mx, p.top_k);
   }
@@ -264,19 +353,30 @@ __device__ __forceinline__ void entropy_sample_row_wave(const EntropyParams &p, 
     float y[8];
     w.get(y);
     const bool ok = v < nvec;
-    cand_offer(cs, p.top_k, lane, y, (uint32_t)v * 8u, ok ? 8 : 0);
-    if (ok) tri_fold8(t, y, c);
+    const float xm = max8(y);
+    if (__any(ok && xm >= cs.vmin)) cand_offer(cs, p.top_k, lane, y, (uint32_t)v * 8u, ok ? 8 : 0);
+    if (ok) tri_fold8(t, y, xm, c);
+  };
+  // The buffer cut to the k best once it outgrows the wave: with the threshold
+  // at the k-th best of what has streamed, candidates get rare (k per bank, then
+  // k/2, k/3 ...) and most vectors are passed over by one vote: 102 us for
+  // 152064 logits beside few attention units, against 135 at the first bank's
+  // threshold until the buffer is full (57 for the entropy alone).
+  auto tighten = [&]() {
+    if (cs.cnt > kWave && cs.cnt > p.top_k) cand_reduce_any(cs, p.top_k, p.top_k, lane);
   };
   for (int v0 = 0; v0 < nvec; v0 += 2 * BANK) {
 #pragma unroll
     for (int u = 0; u < U; u++) b[u].load(rr, v0 + BANK + u * kWave + lane);
 #pragma unroll
     for (int u = 0; u < U; u++) fold(a[u], v0 + u * kWave + lane);
+    tighten();
     if (v0 + BANK >= nvec) break;
 #pragma unroll
     for (int u = 0; u < U; u++) a[u].load(rr, v0 + 2 * BANK + u * kWave + lane);
 #pragma unroll
     for (int u = 0; u < U; u++) fold(b[u], v0 + BANK + u * kWave + lane);
+    tighten();
   }
   {
     // The V % 8 trailing logits, one per lane.
@@ -290,16 +390,51 @@ __device__ __forceinline__ void entropy_sample_row_wave(const EntropyParams &p, 
       tri_add<1>(t, z);
     }
   }
-#pragma unroll
-  for (int msk = 32; msk >= 1; msk >>= 1) {
-    Tri o{shfl_xor(t.m, msk), shfl_xor(t.z, msk), shfl_xor(t.s, msk)};
-    t = tri_merge(t, o);
-  }
-  const float H = finish_entropy(t);
-  if (lane == 0) p.H[row] = H;
-  detector_push(p, row, H, lane);
+  entropy_put(p, row, lane, wave_merge(t));
   if (cs.cnt > p.top_k) cand_reduce_any(cs, p.top_k, p.top_k, lane);  // exactly the k best
   sample_draw(p, row, lane, cs.buf, lds + kCandCap, cs.cnt);
+}
+
+// The same by a workgroup of NW waves, as entropy_row_group; the first wave
+// takes the k best of the waves' candidates. lds: kSampleGroupLds<NW> bytes.
+template <int NW>
+constexpr size_t kSampleGroupLds = (size_t)(NW * kCandCap + 2 * kTopKMax) * sizeof(uint64_t) +
+                                   NW * (sizeof(Tri) + (1 + kWave) * sizeof(int));
+
+template <typename T, int U, int NW>
+__device__ __forceinline__ void entropy_sample_row_group(const EntropyParams &p, int row, int lane, int wave,
+                                                         uint64_t *lds) {
+  uint64_t *win = lds + NW * kCandCap, *sorted = win + kTopKMax;
+  uint32_t *lane_max = reinterpret_cast<uint32_t *>(sorted + kTopKMax);
+  Tri *part = reinterpret_cast<Tri *>(lane_max + NW * kWave);
+  int *cand_n = reinterpret_cast<int *>(part + NW);
+  const int nvec = p.V / 8, per = (nvec + NW - 1) / NW;
+  const int v0 = min(wave * per, nvec), v1 = min(v0 + per, nvec);
+  const bool last = wave == NW - 1;
+  float mx = kNegInf;
+  Tri t = entropy_fold_wave<T, U>(p, row, lane, v0, v1, last, mx);
+  lane_max[wave * kWave + lane] = order_bits(mx);
+  if (lane == 0) part[wave] = t;
+  __syncthreads();
+  const float bound = group_bound<NW>(lane_max, lane, p.top_k);
+  Cands cs{lds + wave * kCandCap, 0, 1, bound};
+  offer_wave<T, U>(p, row, lane, v0, v1, last, cs);
+  if (lane == 0) cand_n[wave] = cs.cnt;
+  __syncthreads();
+  if (wave != 0) return;
+  t = part[0];
+  int off[NW + 1];
+  off[0] = 0;
+#pragma unroll
+  for (int w = 0; w < NW; w++) {
+    if (w) t = tri_merge(t, part[w]);
+    off[w + 1] = off[w] + cand_n[w];
+  }
+  entropy_put(p, row, lane, t);
+  int nwin;
+  if (off[NW] <= kWave) nwin = gather_select<1, NW>(lds, off, p.top_k, lane, win);
+  else nwin = gather_select<NW * kTopKMax / kWave, NW>(lds, off, p.top_k, lane, win);
+  sample_draw(p, row, lane, win, sorted, nwin);
 }
 
 }  // namespace

@@ -9,6 +9,8 @@ may take either side, so the GPU token must then be a member of the oracle's
 top-k, at most one position from the oracle's pick in the sorted order.
 Entropy within 1e-4 absolute; detector state equal.
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -160,3 +162,51 @@ def test_sampler_rejects_bad_settings():
             k.logit_entropy_sample(x, H, tok, smp, workspace=ws)
     with pytest.raises(k.KvrError):
         k.logit_entropy_sample(x, H, tok, k.Sampler(), workspace=None)
+
+
+@pytest.mark.parametrize("kind", ["normal", "equal", "ninf", "negative", "rising", "clustered"])
+@pytest.mark.parametrize("V,top_k,dt", [
+    (8, 20, torch.float32), (71, 64, torch.bfloat16), (20480, 20, torch.bfloat16), (20485, 20, torch.float32),
+    (40999, 1, torch.bfloat16), (152064, 50, torch.bfloat16),
+    (327680, 64, torch.bfloat16), (327688, 64, torch.bfloat16),  # 16 splits of one round, and one vector more
+])
+def test_sampler_routes_agree(kind, V, top_k, dt):
+    """Rows that start 16-byte aligned (a split in registers at once, or
+    streamed where the splits are longer) and the same rows at a byte offset
+    that they do not (scalar loads) give the same k best logits, so the same
+    tokens; the entropies differ by the order of their float32 sums (1e-5 of a
+    value of at most ln V = 12.7). Rows of equal logits, of rising ones and of
+    a few lanes that hold all the large ones have more candidates than the
+    register route ranks at once; "ninf" rows have fewer finite logits than k."""
+    k = kvr()
+    say("sampler routes", kind, V, top_k, dt)
+    R = 3
+    g = torch.Generator().manual_seed(V + top_k)
+    x = torch.randn((R, V), generator=g) * 3.0
+    if kind == "equal":
+        x.fill_(-1.5)
+    elif kind == "ninf":
+        keep = torch.zeros((R, V), dtype=torch.bool)
+        keep[:, torch.randperm(V, generator=g)[: min(V, 5)]] = True
+        x.masked_fill_(~keep, -math.inf)
+    elif kind == "negative":
+        x = -x.abs() - 50.0
+    elif kind == "rising":
+        x = torch.arange(V, dtype=torch.float32).mul_(1e-3).repeat(R, 1)
+    elif kind == "clustered":
+        x[:, : min(V, 500)] += 30.0
+    x = x.to(dt)
+    ld = (V + 15) // 8 * 8
+    flat = torch.zeros(R * ld + 8, dtype=dt, device=DEV)
+    on, off = flat[: R * ld].view(R, ld), torch.zeros_like(flat)[1: R * ld + 1].view(R, ld)
+    on[:, :V] = x.to(DEV)
+    off[:, :V] = x.to(DEV)
+    assert on.data_ptr() % 16 == 0 and off.data_ptr() % 16 != 0
+    for step in (0, 1, 77):
+        smp = k.Sampler(top_k=top_k, top_p=0.95, temperature=0.8, seed=3, step=step)
+        H, tok = _run(on, V, smp)
+        H2, tok2 = _run(off, V, smp)
+        assert np.array_equal(tok, tok2)
+        assert np.abs(H - H2).max() <= 1e-5 * 12.7
+        if kind in ("normal", "negative", "clustered"):
+            _check_tokens(host(x), V, smp, tok)
