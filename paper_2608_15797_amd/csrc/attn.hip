@@ -341,11 +341,12 @@ __device__ __forceinline__ void chunk_logits_lds(const char *slot, const short4_
 // the chunk at k0. Keys [k0, k1) of kbase / vbase are read. Before a chunk is
 // processed the wave waits until only the loads of the chunks after it are in
 // flight: nothing else is issued inside the loop, so that count is exact.
-template <int D, int TILES, int DEPTH, typename Pre, typename Proc>
+// With NW waves per unit a wave takes every NW-th chunk (k0 is its first).
+template <int D, int TILES, int DEPTH, int NW, typename Pre, typename Proc>
 __device__ __forceinline__ void stream_chunks_lds(VChunk<D, TILES> (&buf)[DEPTH], char *ring, const bf16_t *kbase,
                                                   const bf16_t *vbase, int k0, int k1,
                                                   const KLOffsets<D, TILES> &off, Pre pre, Proc proc) {
-  constexpr int stride = 16 * TILES;
+  constexpr int stride = 16 * TILES * NW;
   constexpr int SLOT = 16 * TILES * KLds<D>::ROW;
   constexpr int PER = KLOffsets<D, TILES>::KI + 4 * TILES;  // instructions per chunk
 #pragma unroll
@@ -700,7 +701,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void at
       load_chunk<D, TILES>(ring[0], Kr, Vr, 0, r16, g4);
   }
   if constexpr (KL)
-    stream_chunks_lds<D, TILES, DEPTH>(vring, kring, Kc, Vc, 0, ncache, kloff, new_token,
+    stream_chunks_lds<D, TILES, DEPTH, 1>(vring, kring, Kc, Vc, 0, ncache, kloff, new_token,
                                        [&](VChunk<D, TILES> &c, const char *slot, int c0) { process(c, slot, c0, ncache); });
   else
     stream_chunks_from<D, TILES, DEPTH>(ring, Kr, Vr, 0, ncache, r16, g4, new_token,
@@ -842,6 +843,292 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void at
     }
   }
 }
+
+#if !KVR_ATTN_WIDE
+// Own-cache kernel for launches of few units (one layer at a time, few
+// candidates, the suffixes of a few helper contexts): kSplitWaves waves per
+// unit, each with every kSplitWaves-th chunk of 16 keys through a key ring of
+// its own. Bound by the length of a unit's chain (live length, chunks,
+// epilogue) and not by bytes: one wave per unit leaves the chip a wave or two
+// per CU, and a suffix of 512 tokens is 16 chunks one after another. The
+// waves' partial outputs, maxima and sums meet in LDS (each in its own, used
+// up, ring), and a thread finishes 8 columns of a row. MERGE folds in the
+// context kernel's partials there: a thread's share of the first kFastPieces
+// records is loaded before the stream.
+constexpr int kSplitWaves = 4;
+constexpr int kSplitTiles = 1;
+constexpr int kSplitDepth = 3;
+
+template <int D>
+constexpr size_t split_ring = kl_ring<D, kSplitTiles, kSplitDepth>;  // of one wave
+// Rings, then each wave's row maxima and sums, the rows' merged ones, the new token's logits.
+template <int D>
+constexpr size_t split_lds = kSplitWaves * split_ring<D> + (2 * kSplitWaves + 3) * 16 * sizeof(float);
+
+template <int D, bool MERGE, int LT>
+__global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(2))) void attn_cache_split_bf16(
+    AttnParams p, EntropyBatch e) {
+  constexpr int NW = kSplitWaves, CH = 16 * kSplitTiles, DEPTH = kSplitDepth;
+  constexpr int NB = Geo<D>::NB;
+  constexpr int NT = 64 * NW;
+  constexpr uint32_t ROW = D * 2;
+  static_assert(16 * D * sizeof(float) <= split_ring<D>, "a wave's partial outputs take the place of its ring");
+  static_assert(16 * (D / 8) <= NT, "one thread per 8 output columns");
+  extern __shared__ float smem[];
+  const int tid = threadIdx.x;
+  const int lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+
+  int unit = blockIdx.x;  // ((s * L) + l) * Hkv + h
+  if constexpr (LT != 0) {
+    const int rows = e.row0[e.nsets];
+    if (unit < rows) {
+      const int k = batch_set(e, unit), row = unit - e.row0[k];
+      if constexpr (LT == 1) entropy_row_group<bf16_t, 12, NW>(e.set[k], row, lane, wave, reinterpret_cast<Tri *>(smem));
+      else if constexpr (LT == 2) entropy_row_group<float, 6, NW>(e.set[k], row, lane, wave, reinterpret_cast<Tri *>(smem));
+      else if constexpr (LT == 3)
+        entropy_sample_row_group<bf16_t, 8, NW>(e.set[k], row, lane, wave, reinterpret_cast<uint64_t *>(smem));
+      else
+        entropy_sample_row_group<float, 4, NW>(e.set[k], row, lane, wave, reinterpret_cast<uint64_t *>(smem));
+      return;
+    }
+    unit -= rows;
+  }
+  const int h = unit % p.Hkv;
+  const int sl = unit / p.Hkv;
+  const int l = sl % p.L;
+  const int s = sl / p.L;
+  const int r16 = lane & 15;
+  const int g4 = lane >> 4;
+  const int G = p.G;
+  const int qh0 = h * G;
+  const size_t qrow0 = ((size_t)s * p.L + l) * p.Hq + qh0;
+  const size_t ubase = (size_t)unit * p.cap * D;
+  bf16_t *Kc = static_cast<bf16_t *>(p.k) + ubase;
+  bf16_t *Vc = static_cast<bf16_t *>(p.v) + ubase;
+  const bool has_new = p.k_new != nullptr && wave == 0;  // the first wave takes the new token
+
+  // As in the one-wave kernel, the loads that do not depend on the live
+  // length go first: the query rows, the new token's rows and, for an evicted
+  // cache, the wave's first chunk (stale rows masked and zeroed below).
+  short4_t qop[NB];
+  load_qop<D>(r16 < G ? static_cast<const bf16_t *>(p.q) + (qrow0 + r16) * D : nullptr, g4, qop);
+  KVChunk<D, 1> cn;
+  if (has_new)
+    load_chunk<D, 1>(cn, make_rsrc(static_cast<const bf16_t *>(p.k_new) + (size_t)unit * D, ROW),
+                     make_rsrc(static_cast<const bf16_t *>(p.v_new) + (size_t)unit * D, ROW), 0, r16, g4);
+  VChunk<D, kSplitTiles> vring[DEPTH];
+  char *kring = reinterpret_cast<char *>(smem) + wave * split_ring<D>;
+  const KLOffsets<D, kSplitTiles> kloff(lane);
+  const int k0 = wave * CH;
+  if constexpr (!MERGE) {
+    const int first = p.cap < k0 + CH ? p.cap : k0 + CH;
+    load_chunk_lds<D, kSplitTiles>(vring[0], kring, Kc, Vc, first, k0, kloff);
+  }
+
+  int n = p.len[s];
+  n = n < 0 ? 0 : (n > p.cap ? p.cap : n);
+  const bool append = p.k_new != nullptr && n >= 1;
+  const bool put_pos = append && p.pos != nullptr && p.new_pos != nullptr;
+  const int32_t npos = put_pos ? p.new_pos[s] : 0;
+  const int ncache = append ? n - 1 : n;
+
+  // This thread's 8 output columns (threads past G * D / 8: none) and, with
+  // MERGE, its share of the row's first context partials.
+  const int orow = tid / (D / 8), ocol = 8 * (tid % (D / 8));
+  constexpr int RF = kRecFloats<D>;
+  int npieces = 0;
+  const size_t rstride = (size_t)p.S * p.L * p.Hq * RF;
+  const float *rbase = nullptr;
+  float2_t pms[kFastPieces];
+  u32x4 phv[kFastPieces];
+  if constexpr (MERGE) {
+    const long ug = ((long)((s / p.C) * p.L + l) * p.Hkv + h) * p.plen;
+    npieces = (int)((ug + p.plen - 1) / p.span - ug / p.span) + 1;
+    rbase = p.ws + (qrow0 + orow) * RF;
+#pragma unroll
+    for (int k = 0; k < kFastPieces; k++) {
+      pms[k] = float2_t{kNegInf, 0.f};
+      phv[k] = u32x4{0u, 0u, 0u, 0u};
+      if (orow < G && k < npieces) {
+        pms[k] = *reinterpret_cast<const float2_t *>(rbase + k * rstride);
+        phv[k] = *reinterpret_cast<const u32x4 *>(rbase + k * rstride + 4 + ocol / 2);
+      }
+    }
+    load_chunk_lds<D, kSplitTiles>(vring[0], kring, Kc, Vc, ncache, k0, kloff);
+  }
+
+  // Observation-window step of this sequence?
+  const int wstart = p.B + p.buffer + 2 - p.W;
+  const bool win = !MERGE && p.scores != nullptr && n >= wstart;
+  const int ldx = (p.cap + 63) & ~63;
+  float *wm = smem + NW * split_ring<D> / sizeof(float);  // [NW][16] the waves' row maxima
+  float *wz = wm + NW * 16;                               // [NW][16] and sums
+  float *stat = wz + NW * 16;                             // [16] max, [16] 1/sum
+  float *xn = stat + 32;                                  // [16] the new token's logits
+  float *xs = xn + 16;                                    // [G][ldx] logits of window steps
+
+  const float sl2 = p.scale * kLog2e;
+  RowState st{kNegInf, 0.0f};
+  float4_t o[NB];
+#pragma unroll
+  for (int b = 0; b < NB; b++) o[b] = float4_t{0.f, 0.f, 0.f, 0.f};
+
+  auto process = [&](VChunk<D, kSplitTiles> &c, const char *kslot, int c0) {
+    if (!MERGE && c0 == k0 && ncache < c0 + CH) {
+      // The first chunk was read before the live length was known.
+#pragma unroll
+      for (int cc = 0; cc < 4; cc++)
+        if (c0 + 4 * g4 + cc >= ncache)
+#pragma unroll
+          for (int w = 0; w < Geo<D>::VW; w++) c.v[0][cc][w] = 0u;
+    }
+    float x[1][4];
+    chunk_logits_lds<D, 1>(kslot, qop, x, c0, ncache, r16, g4, sl2, c0 + CH > ncache);
+    if (win && r16 < G)
+      *reinterpret_cast<float4_t *>(xs + r16 * ldx + c0 + 4 * g4) = float4_t{x[0][0], x[0][1], x[0][2], x[0][3]};
+    softmax_pv<D, 1, true>(x, st, o, c.v, g4);
+  };
+
+  // Stored scores of window steps that accumulate, prefetched.
+  constexpr int PRE = 2;  // per thread (slots < 512)
+  const bool accumulate = win && n != wstart;
+  float old[PRE];
+  float *sc = win ? p.scores + (size_t)unit * p.cap : nullptr;
+  if (accumulate) {
+    const rsrc_t Sr = make_rsrc(sc, (uint32_t)(n - 1) * 4u);
+#pragma unroll
+    for (int k = 0; k < PRE; k++)
+      old[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(Sr, (uint32_t)(tid + NT * k) * 4u, 0, 0));
+  }
+  auto new_token = [&]() {
+    if (has_new && append) {
+      if (r16 == 0) {
+#pragma unroll
+        for (int i = 0; i < Geo<D>::NLD; i++)
+          __builtin_nontemporal_store(cn.k[0][i],
+                                      reinterpret_cast<u32x4 *>(Kc + (size_t)(n - 1) * D + 32 * i + 8 * g4));
+      }
+      if (g4 == 0) {
+        bf16_t *vd = Vc + (size_t)(n - 1) * D + r16 * NB;
+        if constexpr (D == 128)
+          __builtin_nontemporal_store(u32x4{cn.v[0][0][0], cn.v[0][0][1], cn.v[0][0][2], cn.v[0][0][3]},
+                                      reinterpret_cast<u32x4 *>(vd));
+        else
+          __builtin_nontemporal_store(u32x2{cn.v[0][0][0], cn.v[0][0][1]}, reinterpret_cast<u32x2 *>(vd));
+      }
+      if (put_pos && lane == 16) __builtin_nontemporal_store(npos, p.pos + (size_t)unit * p.cap + n - 1);
+      float x[1][4];
+      chunk_logits<D, 1>(cn, qop, x, 0, 1, g4, sl2, true);
+      if (g4 == 0) xn[r16] = x[0][0];
+      softmax_pv<D, 1, true>(x, st, o, cn.v, g4);
+    }
+  };
+  stream_chunks_lds<D, kSplitTiles, DEPTH, NW>(vring, kring, Kc, Vc, k0, ncache, kloff, new_token, process);
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_s_waitcnt(0);  // no buffer-to-LDS load outlives the stream
+#endif
+
+  // The wave's partial rows, over its ring.
+  float z = st.zl;
+  z += shfl_xor(z, 16);
+  z += shfl_xor(z, 32);
+  if (g4 == 0) {
+    wm[wave * 16 + r16] = st.m;
+    wz[wave * 16 + r16] = z;
+  }
+  float *part = reinterpret_cast<float *>(kring);
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+    if (4 * g4 + i < G)
+#pragma unroll
+      for (int b = 0; b < NB; b += 4)
+        *reinterpret_cast<float4_t *>(part + (4 * g4 + i) * D + r16 * NB + b) =
+            float4_t{o[b][i], o[b + 1][i], o[b + 2][i], o[b + 3][i]};
+  __syncthreads();
+
+  if (orow < G) {
+    float M = kNegInf;
+#pragma unroll
+    for (int w = 0; w < NW; w++) M = fmaxf(M, wm[w * 16 + orow]);
+    if constexpr (MERGE) {
+#pragma unroll
+      for (int k = 0; k < kFastPieces; k++) M = fmaxf(M, pms[k].x);
+    }
+    float zs = 0.f;
+    float4_t a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+      const float m = wm[w * 16 + orow];
+      const float f = m == kNegInf ? 0.f : fast_exp2(m - M);
+      const float *r = reinterpret_cast<const float *>(reinterpret_cast<const char *>(smem) + w * split_ring<D>) +
+                       orow * D + ocol;
+      zs += wz[w * 16 + orow] * f;
+      a += *reinterpret_cast<const float4_t *>(r) * f;
+      b += *reinterpret_cast<const float4_t *>(r + 4) * f;
+    }
+    if constexpr (MERGE) {
+      // Log-sum-exp merge with the context partials (max, sum, -, -, o / sum).
+      auto fold = [&](float2_t ms, u32x4 hv) {
+        const float f = ms.x == kNegInf ? 0.f : ms.y * fast_exp2(ms.x - M);
+        zs += f;
+        a += float4_t{f16_lo(hv.x), f16_hi(hv.x), f16_lo(hv.y), f16_hi(hv.y)} * f;
+        b += float4_t{f16_lo(hv.z), f16_hi(hv.z), f16_lo(hv.w), f16_hi(hv.w)} * f;
+      };
+#pragma unroll
+      for (int k = 0; k < kFastPieces; k++) fold(pms[k], phv[k]);
+      // Further records in batches, each batch's loads issued together.
+      for (int k0 = kFastPieces; k0 < npieces; k0 += kFastPieces) {
+        float Mb = M;
+#pragma unroll
+        for (int k = 0; k < kFastPieces; k++) {
+          const float *r = rbase + (k0 + k < npieces ? k0 + k : k0) * rstride;
+          pms[k] = *reinterpret_cast<const float2_t *>(r);
+          phv[k] = *reinterpret_cast<const u32x4 *>(r + 4 + ocol / 2);
+        }
+#pragma unroll
+        for (int k = 0; k < kFastPieces; k++) {
+          if (k0 + k >= npieces) pms[k] = float2_t{kNegInf, 0.f};
+          Mb = fmaxf(Mb, pms[k].x);
+        }
+        const float f = M == kNegInf ? 0.f : fast_exp2(M - Mb);
+        zs *= f;
+        a *= f;
+        b *= f;
+        M = Mb;
+#pragma unroll
+        for (int k = 0; k < kFastPieces; k++) fold(pms[k], phv[k]);
+      }
+    }
+    const float inv = 1.0f / zs;
+    if (win && ocol == 0) {
+      stat[orow] = M;
+      stat[16 + orow] = inv;
+    }
+    __builtin_nontemporal_store(u32x4{pack_bf16x2(a[0] * inv, a[1] * inv), pack_bf16x2(a[2] * inv, a[3] * inv),
+                                      pack_bf16x2(b[0] * inv, b[1] * inv), pack_bf16x2(b[2] * inv, b[3] * inv)},
+                                reinterpret_cast<u32x4 *>(static_cast<bf16_t *>(p.out) + (qrow0 + orow) * D + ocol));
+  }
+  if constexpr (!MERGE) {
+    if (win) {
+      __syncthreads();
+      auto mass = [&](int j) {
+        float r = 0.0f;
+        for (int g = 0; g < G; g++)
+          r += fast_exp2((append && j == n - 1 ? xn[g] : xs[g * ldx + j]) - stat[g]) * stat[16 + g];
+        return r;
+      };
+#pragma unroll
+      for (int k = 0; k < PRE; k++) {
+        const int j = tid + NT * k;
+        if (j < n) __builtin_nontemporal_store((accumulate && j < n - 1) ? old[k] + mass(j) : mass(j), sc + j);
+      }
+      for (int j = tid + NT * PRE; j < n; j += NT)
+        __builtin_nontemporal_store((accumulate && j < n - 1) ? sc[j] + mass(j) : mass(j), sc + j);
+    }
+  }
+}
+#endif  // !KVR_ATTN_WIDE
 
 // ---------------------------------------------------------------------------
 // Prefix kernel: each wave walks its span of the flattened (prefix, layer,
@@ -1248,6 +1535,67 @@ void launch_prefix(const AttnParams &p, const EntropyBatch *e, hipStream_t strea
     hipLaunchKernelGGL((attn_prefix_bf16<D, RB, TILES, 2>), dim3(p.nwaves), dim3(64), lds, stream, p);
 }
 
+#if !KVR_ATTN_WIDE
+// Four waves per unit (attn_cache_split_bf16) where the units are few: one per
+// CU, two where a wave has more chunks than its ring, eight suffixes per CU.
+// Measured (7B heads, us, one wave against four): 256 units of 98-129 tokens
+// 7.6 / 6.2, of 129-257 11.2 / 7.5; 512 units 8.4 / 8.4 and 12.4 / 11.2; 1024
+// units 12.0 / 15.4 and 20.4 / 20.3. Suffixes of 1-512 tokens behind contexts:
+// 448 units 12 us less, 1792 5 us less; 3584 of 1-64 tokens 13 us more.
+constexpr long kSplitUnits = 256, kSplitUnitsLong = 512;
+constexpr long kSplitSuffixUnits = 2048;
+
+// Whole logit rows, four waves per row, as a kernel of its own.
+template <typename T, bool SAMPLE>
+__global__ __launch_bounds__(64 * kSplitWaves) void entropy_rows_kernel(EntropyBatch e) {
+  extern __shared__ uint64_t row_lds[];
+  const int g = blockIdx.x;
+  const int k = batch_set(e, g);
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if constexpr (SAMPLE)
+    entropy_sample_row_group<T, sizeof(T) == 2 ? 8 : 4, kSplitWaves>(e.set[k], g - e.row0[k], lane, wave, row_lds);
+  else
+    entropy_row_group<T, sizeof(T) == 2 ? 12 : 6, kSplitWaves>(e.set[k], g - e.row0[k], lane, wave,
+                                                              reinterpret_cast<Tri *>(row_lds));
+}
+
+void launch_rows(const EntropyBatch &e, hipStream_t stream) {
+  const dim3 rows(e.row0[e.nsets]), block(64 * kSplitWaves);
+  const bool sample = e.set[0].top_k > 0;
+  const size_t lds = sample ? kSampleGroupLds<kSplitWaves> : kSplitWaves * sizeof(Tri);
+  if (e.set[0].dtype == 0) {
+    if (sample) hipLaunchKernelGGL((entropy_rows_kernel<float, true>), rows, block, lds, stream, e);
+    else hipLaunchKernelGGL((entropy_rows_kernel<float, false>), rows, block, lds, stream, e);
+  } else {
+    if (sample) hipLaunchKernelGGL((entropy_rows_kernel<bf16_t, true>), rows, block, lds, stream, e);
+    else hipLaunchKernelGGL((entropy_rows_kernel<bf16_t, false>), rows, block, lds, stream, e);
+  }
+}
+
+// The same with and without logit rows, whose call promises the same bits.
+template <int D>
+bool split_own(const AttnParams &p, size_t logits) {
+  const long units = (long)p.S * p.L * p.Hkv;
+  return split_lds<D> + logits <= kMaxLds &&
+         (units <= kSplitUnits || (units <= kSplitUnitsLong && p.cap > 16 * kSplitTiles * kSplitDepth * kSplitWaves));
+}
+
+// The kernel of few units, rows as in launch_own.
+template <int D, bool MERGE>
+void launch_split(const AttnParams &p, const EntropyBatch *e, size_t lds, hipStream_t stream) {
+  const int rows = e ? e->row0[e->nsets] : 0;
+  const dim3 grid(rows + p.S * p.L * p.Hkv), block(64 * kSplitWaves);
+  const EntropyBatch none{};
+  const bool f32 = e && e->set[0].dtype == 0;
+  const bool sample = e && e->set[0].top_k > 0;
+  static_assert(split_lds<64> >= kSampleGroupLds<kSplitWaves>, "the rows' candidate buffers fit");
+  if (!e) hipLaunchKernelGGL((attn_cache_split_bf16<D, MERGE, 0>), grid, block, lds, stream, p, none);
+  else if (sample && f32) hipLaunchKernelGGL((attn_cache_split_bf16<D, MERGE, 4>), grid, block, lds, stream, p, *e);
+  else if (sample) hipLaunchKernelGGL((attn_cache_split_bf16<D, MERGE, 3>), grid, block, lds, stream, p, *e);
+  else if (f32) hipLaunchKernelGGL((attn_cache_split_bf16<D, MERGE, 2>), grid, block, lds, stream, p, *e);
+  else hipLaunchKernelGGL((attn_cache_split_bf16<D, MERGE, 1>), grid, block, lds, stream, p, *e);
+}
+
 // The evicted-cache kernel with the entropy rows of `e` (nullptr: none) in
 // front of its units.
 template <int D, int TILES, int DEPTH, bool KL>
@@ -1290,7 +1638,10 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
     const size_t logits = p.scores ? ((size_t)p.G * ((p.cap + 63) & ~63) + 32) * sizeof(float) : 0;
     const size_t lds_min = D == 128 ? kBaseLdsFloor : 0;
     constexpr size_t ring = kl_ring<D, kKlTiles, kKlDepth>;
-    if (ring + logits <= kMaxLds) {
+    const bool split = split_own<D>(p, logits);
+    if (split) {
+      launch_split<D, false>(p, ent, split_lds<D> + logits, stream);
+    } else if (ring + logits <= kMaxLds) {
       // Key rows through the LDS ring. No floor here: with the keys in LDS,
       // 7-8 workgroups per CU (registers: 172) measured 1-1.5% faster than the
       // 6 of a 26 KiB floor on the 7B shapes and equal on the 72B shape.
@@ -1313,7 +1664,9 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
   if (e != hipSuccess) return e;
   const size_t pre = (size_t)p.merge_pf * p.merge_blk * sizeof(float);
   constexpr size_t ring = kl_ring<D, kKlTiles, kKlDepth>;
-  if constexpr (kSuffixKl)
+  if ((long)p.S * p.L * p.Hkv <= kSplitSuffixUnits)
+    launch_split<D, true>(p, nullptr, split_lds<D>, stream);
+  else if constexpr (kSuffixKl)
     hipLaunchKernelGGL((attn_cache_bf16<D, true, kKlTiles, kKlDepth, true>), units, dim3(64), ring + pre, stream, p,
                        EntropyBatch{});
   else
@@ -1321,7 +1674,6 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
   return hipGetLastError();
 }
 
-#if !KVR_ATTN_WIDE
 template <int D>
 void launch_f32(const AttnParams &p, hipStream_t stream) {
   // Logit rows of nt tokens, padded to 16 bytes (one read for four tokens)
@@ -1339,19 +1691,6 @@ void launch_f32(const AttnParams &p, hipStream_t stream) {
   else hipLaunchKernelGGL((attn_f32<D, 16>), grid, dim3(kF32Threads), lds, stream, p, (int)ld, (int)stat);
 }
 #endif  // !KVR_ATTN_WIDE
-
-// Whole logit rows, one wave per row, as a kernel of its own (the entropy
-// rows of a float32-cache launch, whose attention kernel has no such lanes).
-template <typename T, bool SAMPLE>
-__global__ __launch_bounds__(64) void entropy_rows_kernel(EntropyBatch e) {
-  extern __shared__ uint64_t cand[];
-  const int g = blockIdx.x;
-  const int k = batch_set(e, g);
-  if constexpr (SAMPLE)
-    entropy_sample_row_wave<T, sizeof(T) == 2 ? 8 : 4>(e.set[k], g - e.row0[k], threadIdx.x, cand);
-  else
-    entropy_row_wave<T, sizeof(T) == 2 ? 12 : 6>(e.set[k], g - e.row0[k], threadIdx.x);
-}
 
 }  // namespace
 
@@ -1439,16 +1778,7 @@ hipError_t launch_decode_attn(const AttnParams &p, const EntropyBatch *ent, hipS
     else launch_f32<64>(p, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !ent) return e;
-    const dim3 rows(ent->row0[ent->nsets]);
-    const bool sample = ent->set[0].top_k > 0;
-    const size_t rlds = sample ? kSampleRowLds : 0;
-    if (ent->set[0].dtype == 0) {
-      if (sample) hipLaunchKernelGGL((entropy_rows_kernel<float, true>), rows, dim3(64), rlds, stream, *ent);
-      else hipLaunchKernelGGL((entropy_rows_kernel<float, false>), rows, dim3(64), 0, stream, *ent);
-    } else {
-      if (sample) hipLaunchKernelGGL((entropy_rows_kernel<bf16_t, true>), rows, dim3(64), rlds, stream, *ent);
-      else hipLaunchKernelGGL((entropy_rows_kernel<bf16_t, false>), rows, dim3(64), 0, stream, *ent);
-    }
+    launch_rows(*ent, stream);
     return hipGetLastError();
   }
   return p.D == 128 ? launch_bf16<128>(p, ent, stream) : launch_bf16<64>(p, ent, stream);

@@ -236,6 +236,17 @@ def test_decode_attn_prefix_f32_shapes(case):
     test_decode_attn_prefix(case)
 
 
+# Few units: four waves per unit. Live lengths end in every wave's share (chunks of 16 keys), logits in and out of the
+# window, groups of 1 and 16 heads, caches whose stored scores exceed the prefetched ones.
+@pytest.mark.parametrize("case", [
+    (4, 1, 1, 16, 128, 30, 8, 40, torch.bfloat16), (6, 1, 2, 1, 64, 17, 5, 60, torch.bfloat16),
+    (2, 2, 2, 7, 128, 300, 64, 300, torch.bfloat16), (8, 4, 16, 4, 64, 40, 8, 30, torch.bfloat16),
+    (9, 4, 16, 4, 64, 40, 8, 30, torch.bfloat16),
+], ids=lambda c: "S%dL%dHkv%dG%dD%d_B%d" % c[:6])
+def test_decode_attn_few_units(case):
+    test_decode_attn_base_with_scores(case)
+
+
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
 def test_decode_attn_prefix_empty_suffix(dt):
     """A sequence without live slots (len 0) attends to its context alone: the
