@@ -595,7 +595,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void at
   const size_t rstride = (size_t)p.S * p.L * p.Hq * RF;
   const float *rbase = nullptr;
   if constexpr (MERGE) {
-    const long ug = ((long)((s / p.C) * p.L + l) * p.Hkv + h) * p.plen;
+    const long ug = ((long)((s / p.C) * p.L + l) * p.Hkv + h) * p.pitch;
     npieces = (int)((ug + p.plen - 1) / p.span - ug / p.span) + 1;
     pf = npieces < p.merge_pf ? npieces : p.merge_pf;
     rbase = p.ws + (((size_t)s * p.L + l) * p.Hq + qh0) * RF;
@@ -943,7 +943,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
   float2_t pms[kFastPieces];
   u32x4 phv[kFastPieces];
   if constexpr (MERGE) {
-    const long ug = ((long)((s / p.C) * p.L + l) * p.Hkv + h) * p.plen;
+    const long ug = ((long)((s / p.C) * p.L + l) * p.Hkv + h) * p.pitch;
     npieces = (int)((ug + p.plen - 1) / p.span - ug / p.span) + 1;
     rbase = p.ws + (qrow0 + orow) * RF;
 #pragma unroll
@@ -1148,7 +1148,7 @@ __device__ __forceinline__ void prefix_wave(const AttnParams &p, const int wave,
   constexpr int CH = 16 * TILES;
   constexpr int NB = Geo<D>::NB;
   constexpr uint32_t ROW = D * 2;
-  const long total = (long)p.P * p.L * p.Hkv * p.plen;
+  const long total = (long)p.P * p.L * p.Hkv * p.pitch;
   const long g0 = (long)wave * p.span;
   const long g1 = g0 + p.span < total ? g0 + p.span : total;
   const int lane = threadIdx.x;
@@ -1162,11 +1162,12 @@ __device__ __forceinline__ void prefix_wave(const AttnParams &p, const int wave,
   // per unit it touches; each segment leaves one partial record per row.
 #pragma clang loop unroll(disable)
   for (long g = g0; g < g1;) {
-  const int unit = (int)(g / p.plen);  // ((pp * L) + l) * Hkv + h
-  const int k0 = (int)(g - (long)unit * p.plen);
-  const int k1 = (int)((long)p.plen < k0 + (g1 - g) ? (long)p.plen : k0 + (g1 - g));
-  const int split = wave - (int)((long)unit * p.plen / p.span);  // piece index within the unit
-  g += k1 - k0;
+  const int unit = (int)(g / p.pitch);  // ((pp * L) + l) * Hkv + h
+  const int k0 = (int)(g - (long)unit * p.pitch);
+  const int ke = (int)((long)p.pitch < k0 + (g1 - g) ? (long)p.pitch : k0 + (g1 - g));
+  const int k1 = ke < p.plen ? ke : p.plen;
+  const int split = wave - (int)((long)unit * p.pitch / p.span);  // piece index within the unit
+  g += ke - k0;
   const int h = unit % p.Hkv;
   const int pl = unit / p.Hkv;
   const int l = pl % p.L;
@@ -1638,8 +1639,7 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
     const size_t logits = p.scores ? ((size_t)p.G * ((p.cap + 63) & ~63) + 32) * sizeof(float) : 0;
     const size_t lds_min = D == 128 ? kBaseLdsFloor : 0;
     constexpr size_t ring = kl_ring<D, kKlTiles, kKlDepth>;
-    const bool split = split_own<D>(p, logits);
-    if (split) {
+    if (split_own<D>(p, logits)) {
       launch_split<D, false>(p, ent, split_lds<D> + logits, stream);
     } else if (ring + logits <= kMaxLds) {
       // Key rows through the LDS ring. No floor here: with the keys in LDS,
@@ -1741,17 +1741,30 @@ long slots_for(int D, int rb, bool rows) {
 
 #if !KVR_ATTN_WIDE
 
-void plan_prefix_splits(int D, int P, int L, int Hkv, int plen, int rows, int ent_rows, int *nsplit, int *span,
-                        int *nwaves) {
+// Span that a context wave need not go below: its chain of 32-key chunks gets
+// shorter with the span, the folding of the records longer with their number
+// per unit, so the best one grows with the square root of plen. Powers of two:
+// 224 keys of 4096 measured 5% slower than either 160 or 256, 448 of 16384
+// slower than 320 and 512. Where the suffix kernel with one wave per unit folds
+// the records (whole loops for more than kFastPieces of them) 512 is as good
+// as any.
+static long least_span(int plen, long units) {
+  if (units > kSplitSuffixUnits || plen > 8192) return 512;
+  return plen > 2048 ? 256 : 128;
+}
+
+void plan_prefix_splits(int D, int S, int P, int L, int Hkv, int plen, int rows, int ent_rows, int *nsplit,
+                        int *span, int *nwaves, int *pitch) {
   // One round of waves: as many as fit on the chip at once, each taking an
-  // equal span (whole 32-key chunks, at least 512 keys) of the flattened
-  // (prefix, layer, KV head, key) space. A unit of plen keys is then covered
-  // by at most ceil(plen / span) + 1 spans. Logit-row waves in the same
-  // launch take their slots first (the context waves keep at least half), and
-  // the context waves never outnumber those of the plan without rows, so that
-  // plan's workspace size covers both.
+  // equal span (whole 32-key chunks) of the flattened (prefix, layer, KV head,
+  // key) space. A unit of plen keys is then covered by at most
+  // ceil(plen / span) + 1 spans. Logit-row waves in the same launch take their
+  // slots first (the context waves keep at least half), and the context waves
+  // never outnumber those of the plan without rows, so that plan's workspace
+  // size covers both.
   const int rb = (rows + 15) / 16;
-  const long total = (long)P * L * Hkv * plen;
+  const long heads = (long)P * L * Hkv;
+  const long total = heads * plen;
   long slots = slots_for(D, rb, false);
   if (ent_rows > 0) {
     const long with_rows = slots_for(D, rb, true);
@@ -1761,11 +1774,22 @@ void plan_prefix_splits(int D, int P, int L, int Hkv, int plen, int rows, int en
   }
   long sp = (total + slots - 1) / slots;
   sp = (sp + 31) / 32 * 32;
-  if (sp < 512) sp = 512;
-  const long nw = (total + sp - 1) / sp;
+  const long least = least_span(plen, (long)S * L * Hkv);
+  *pitch = plen;
+  *nsplit = (int)((plen + (sp > least ? sp : least) - 1) / (sp > least ? sp : least) + 1);
+  if (sp < least && heads <= slots) {
+    // Fewer keys than fill the chip: a unit is cut into equal pieces of its
+    // own (its keys padded to whole spans in the flattened space), so that no
+    // wave has the end of one unit and the start of the next.
+    long pieces = (plen + least - 1) / least;
+    if (pieces > slots / heads) pieces = slots / heads;
+    sp = ((plen + pieces - 1) / pieces + 31) / 32 * 32;
+    *pitch = (int)((plen + sp - 1) / sp * sp);
+  } else if (sp < least) {
+    sp = least;
+  }
   *span = (int)sp;
-  *nwaves = (int)nw;
-  *nsplit = (int)((plen + sp - 1) / sp + 1);
+  *nwaves = (int)((heads * *pitch + sp - 1) / sp);
 }
 
 size_t attn_workspace_bytes(int S, int L, int Hq, int D, int nsplit) {

@@ -31,8 +31,9 @@ struct AttnParams {
   // The context kernel's nwaves waves each take `span` consecutive keys of
   // the flattened (prefix, layer, KV head, key) space; a unit is covered by at
   // most nsplit of them, each leaving one partial record.
+  // A unit takes `pitch` keys of that space: plen, or plen padded to whole spans.
   float *ws;
-  int nsplit, span, nwaves;
+  int nsplit, span, nwaves, pitch;
   // The suffix kernel prefetches the first merge_pf pieces of its rows'
   // partials into LDS (merge_blk floats per piece) at wave start.
   int merge_pf, merge_blk;
@@ -42,8 +43,8 @@ struct AttnParams {
 // ent_rows = logit rows computed in the context launch, 0 for none);
 // identical on the size query and the call. The plan with ent_rows > 0 never
 // has more splits than the one without.
-void plan_prefix_splits(int D, int P, int L, int Hkv, int plen, int rows, int ent_rows, int *nsplit, int *span,
-                        int *nwaves);
+void plan_prefix_splits(int D, int S, int P, int L, int Hkv, int plen, int rows, int ent_rows, int *nsplit,
+                        int *span, int *nwaves, int *pitch);
 size_t attn_workspace_bytes(int S, int L, int Hq, int D, int nsplit);
 
 struct EntropyBatch;

@@ -236,6 +236,20 @@ def test_decode_attn_prefix_f32_shapes(case):
     test_decode_attn_prefix(case)
 
 
+# Work plans of the context: spans over several units (more units than waves fit), spans that cross a unit's end on a
+# full chip, and pieces of a unit's own (odd lengths, more than the records of one batch; one and four waves per suffix).
+@pytest.mark.parametrize("case", [
+    (40, 40, 60, 2, 2, 64, 70, 5, torch.bfloat16),
+    (30, 30, 20, 2, 2, 64, 1000, 40, torch.bfloat16),
+    (1, 1, 1, 1, 3, 128, 33, 70, torch.bfloat16),
+    (2, 1, 1, 2, 6, 128, 4001, 512, torch.bfloat16),
+    (3, 3, 1, 1, 16, 64, 16384, 100, torch.bfloat16),
+    (64, 8, 10, 4, 4, 64, 700, 30, torch.bfloat16),
+], ids=lambda c: "S%dP%dL%dHkv%dD%d_plen%d" % (*c[:4], *c[5:7]))
+def test_decode_attn_prefix_plans(case):
+    test_decode_attn_prefix(case)
+
+
 # Few units: four waves per unit. Live lengths end in every wave's share (chunks of 16 keys), logits in and out of the
 # window, groups of 1 and 16 heads, caches whose stored scores exceed the prefetched ones.
 @pytest.mark.parametrize("case", [
