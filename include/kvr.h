@@ -317,15 +317,18 @@ size_t kvr_logit_entropy_batch_workspace_size(const kvr_logit_set *sets, int32_t
  * ..., workspace) and of kvr_logit_entropy_batch (sets, nsets), with one more
  * requirement: every set's rows start 16-byte aligned (logits and ld *
  * element size), KVR_EINVAL otherwise. Each logit row is reduced whole by one
- * wavefront of the launch, so the rows need no workspace.
- *   Without a prefix the rows ride in the own-cache launch, and the attention
+ * wavefront or workgroup, so the rows need no workspace.
+ *   Without a prefix the rows ride in the own-cache launch (or, where they
+ *   would outlast it, in a launch of their own before it), and the attention
  *   outputs and scores are bit for bit those of kvr_decode_attn.
- *   With a prefix (bfloat16 cache) they ride in the context launch, whose
- *   split plan gives their wavefronts slots of their own (at most half of
- *   the chip's), so the context is cut at other points than kvr_decode_attn
- *   cuts it: the outputs agree with kvr_decode_attn's to the rounding of
- *   the split partials. The workspace size is kvr_decode_attn_workspace_size
- *   (cache, prefix, Hq), which covers this plan.
+ *   With a prefix (bfloat16 cache) they ride in the suffix launch where the
+ *   context is read faster than a wavefront reads a row. Otherwise they ride
+ *   in the context launch, whose split plan gives their wavefronts slots of
+ *   their own (at most half of the chip's), so the context is cut at other
+ *   points than kvr_decode_attn cuts it: the outputs agree with
+ *   kvr_decode_attn's to the rounding of the split partials. The workspace
+ *   size is kvr_decode_attn_workspace_size (cache, prefix, Hq), which covers
+ *   both plans.
  * The entropies agree with kvr_logit_entropy_batch to float32 rounding
  * (different summation order). For a float32 cache the entropy rows run as
  * a second kernel on the same stream.
@@ -351,8 +354,7 @@ int kvr_decode_attn_entropy(const kvr_cache *cache, const kvr_prefix *prefix, co
  * tokens are those kvr_logit_entropy_sample draws from the same rows with the
  * same settings (both take the k largest logits, ties to the lower id, and
  * the same draw). Errors: KVR_EINVAL also for sampler settings out of range
- * or a NULL tokens array or entry. Each row wave keeps its candidates in
- * 2 KiB of its LDS.
+ * or a NULL tokens array or entry.
  */
 int kvr_decode_attn_entropy_sample(const kvr_cache *cache, const kvr_prefix *prefix, const int32_t *len,
                                    const void *q, int32_t Hq, float scale, const void *k_new, const void *v_new,

@@ -92,12 +92,12 @@ size_t kvr_decode_attn_workspace_size(const kvr_cache *cache, const kvr_prefix *
 
 namespace {
 
-// Validates the arguments of kvr_decode_attn and fills p; ent_rows logit rows
-// ride in the same launch (0: none).
+// Validates the arguments of kvr_decode_attn and fills p; ent: the logit rows
+// that ride in the same call (NULL: none).
 int attn_params(const kvr_cache *cache, const kvr_prefix *prefix, const int32_t *len, const void *q, int32_t Hq,
                 float scale, const void *k_new, const void *v_new, const int32_t *new_pos, void *out,
-                const kvr_policy *policy, float *scores, void *workspace, size_t workspace_bytes, int ent_rows,
-                kvr::AttnParams *pp) {
+                const kvr_policy *policy, float *scores, void *workspace, size_t workspace_bytes,
+                const kvr::EntropyBatch *ent, kvr::AttnParams *pp) {
   kvr::AttnParams &p = *pp;
   int G = 0;
   int st = check_cache(cache, Hq, &G);
@@ -140,6 +140,8 @@ int attn_params(const kvr_cache *cache, const kvr_prefix *prefix, const int32_t 
     if (cache->dtype == KVR_BF16) {
       if (p.C * G > 64)
         return fail(KVR_EUNSUPPORTED, "%d candidates x %d heads per shared prefix exceeds 64 rows", p.C, G);
+      p.rows_late = ent && kvr::rows_with_suffix(p, *ent);
+      const int ent_rows = ent && !p.rows_late ? ent->row0[ent->nsets] : 0;
       kvr::plan_prefix_splits(p.D, p.S, p.P, p.L, p.Hkv, p.plen, p.C * G, ent_rows, &p.nsplit, &p.span, &p.nwaves,
                               &p.pitch);
       const size_t need = kvr::attn_workspace_bytes(p.S, p.L, Hq, p.D, p.nsplit);
@@ -167,7 +169,7 @@ int kvr_decode_attn(const kvr_cache *cache, const kvr_prefix *prefix, const int3
                     void *workspace, size_t workspace_bytes, hipStream_t stream) {
   kvr::AttnParams p;
   const int st = attn_params(cache, prefix, len, q, Hq, scale, k_new, v_new, new_pos, out, policy, scores,
-                             workspace, workspace_bytes, 0, &p);
+                             workspace, workspace_bytes, nullptr, &p);
   if (st) return st;
   return hip_status(kvr::launch_decode_attn(p, nullptr, stream), "kvr_decode_attn launch");
 }
@@ -483,8 +485,10 @@ int fused_params(const kvr_cache *cache, const kvr_prefix *prefix, const int32_t
   size_t need = 0;
   int st = entropy_batch(sets, nsets, b, &need);
   if (st) return st;
+  // The plan depends on whether the rows are sampled (checked below).
+  for (int k = 0; k < nsets; k++) b->set[k].top_k = sampler ? sampler->top_k : 0;
   st = attn_params(cache, prefix, len, q, Hq, scale, k_new, v_new, new_pos, out, policy, scores, workspace,
-                   workspace_bytes, b->row0[nsets], p);
+                   workspace_bytes, b, p);
   if (st) return st;
   const size_t esz = sets[0].dtype == KVR_F32 ? 4 : 2;
   for (int k = 0; k < nsets; k++)

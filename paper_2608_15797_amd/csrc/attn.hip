@@ -1546,6 +1546,25 @@ void launch_prefix(const AttnParams &p, const EntropyBatch *e, hipStream_t strea
 constexpr long kSplitUnits = 256, kSplitUnitsLong = 512;
 constexpr long kSplitSuffixUnits = 2048;
 
+// A logit row takes one wave about as long as the chip needs for this many
+// bytes of caches per logit: 50 us for 152064, 102 with the sampler, against 17
+// and 29 for a workgroup of four waves (64 rows each).
+constexpr double kRowBytes = 1900, kSampleRowBytes = 3800;
+// One-wave rows of an evicted-cache launch are worth a launch of their own,
+// four waves per row, where its units take less than this share of a row
+// (their bytes at full caches): 64 rows with 1024 units (143 MB) 57 us in the
+// launch and 38 apart, with 1536 (214 MB) 59 and 46; sampled, with 1024 units
+// 102 and 51, with 2048 104 and 66. With 7168 units sampled rows cost 5 us in
+// the launch.
+constexpr double kOwnShare = 0.8;
+
+// Whether one-wave rows take longer than a launch that reads `bytes` takes `share` of.
+bool rows_outlast(const EntropyBatch &e, double bytes, double share) {
+  int V = 0;
+  for (int k = 0; k < e.nsets; k++) V = e.set[k].V > V ? e.set[k].V : V;
+  return bytes < share * (e.set[0].top_k > 0 ? kSampleRowBytes : kRowBytes) * V;
+}
+
 // Whole logit rows, four waves per row, as a kernel of its own.
 template <typename T, bool SAMPLE>
 __global__ __launch_bounds__(64 * kSplitWaves) void entropy_rows_kernel(EntropyBatch e) {
@@ -1639,7 +1658,12 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
     const size_t logits = p.scores ? ((size_t)p.G * ((p.cap + 63) & ~63) + 32) * sizeof(float) : 0;
     const size_t lds_min = D == 128 ? kBaseLdsFloor : 0;
     constexpr size_t ring = kl_ring<D, kKlTiles, kKlDepth>;
-    if (split_own<D>(p, logits)) {
+    const bool split = split_own<D>(p, logits);
+    if (ent && !split && rows_outlast(*ent, (double)units.x * p.cap * (4 * D), kOwnShare)) {
+      launch_rows(*ent, stream);
+      ent = nullptr;
+    }
+    if (split) {
       launch_split<D, false>(p, ent, split_lds<D> + logits, stream);
     } else if (ring + logits <= kMaxLds) {
       // Key rows through the LDS ring. No floor here: with the keys in LDS,
@@ -1651,8 +1675,10 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
     }
     return hipGetLastError();
   }
-  // Context splits first (with the logit rows, if any); the suffix kernel
-  // then merges their partials.
+  // Context splits first (with the logit rows, unless they go with the
+  // suffixes); the suffix kernel then merges their partials.
+  const EntropyBatch *late = p.rows_late ? ent : nullptr;
+  if (late) ent = nullptr;
   switch ((p.C * p.G + 15) / 16) {
     case 1: launch_prefix<D, 1, 2>(p, ent, stream); break;
     case 2: launch_prefix<D, 2, 2>(p, ent, stream); break;
@@ -1665,7 +1691,7 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
   const size_t pre = (size_t)p.merge_pf * p.merge_blk * sizeof(float);
   constexpr size_t ring = kl_ring<D, kKlTiles, kKlDepth>;
   if ((long)p.S * p.L * p.Hkv <= kSplitSuffixUnits)
-    launch_split<D, true>(p, nullptr, split_lds<D>, stream);
+    launch_split<D, true>(p, late, split_lds<D>, stream);
   else if constexpr (kSuffixKl)
     hipLaunchKernelGGL((attn_cache_bf16<D, true, kKlTiles, kKlDepth, true>), units, dim3(64), ring + pre, stream, p,
                        EntropyBatch{});
@@ -1790,6 +1816,11 @@ void plan_prefix_splits(int D, int S, int P, int L, int Hkv, int plen, int rows,
   }
   *span = (int)sp;
   *nwaves = (int)((heads * *pitch + sp - 1) / sp);
+}
+
+bool rows_with_suffix(const AttnParams &p, const EntropyBatch &e) {
+  return (long)p.S * p.L * p.Hkv <= kSplitSuffixUnits &&
+         rows_outlast(e, (double)p.P * p.L * p.Hkv * p.plen * (4 * p.D), 1.0);
 }
 
 size_t attn_workspace_bytes(int S, int L, int Hq, int D, int nsplit) {

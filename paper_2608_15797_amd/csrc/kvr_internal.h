@@ -37,6 +37,7 @@ struct AttnParams {
   // The suffix kernel prefetches the first merge_pf pieces of its rows'
   // partials into LDS (merge_blk floats per piece) at wave start.
   int merge_pf, merge_blk;
+  int rows_late;  // the call's logit rows go with the suffix launch (rows_with_suffix)
 };
 
 // Work plan of the prefix path (rows = C * G query rows per prefix unit;
@@ -48,6 +49,10 @@ void plan_prefix_splits(int D, int S, int P, int L, int Hkv, int plen, int rows,
 size_t attn_workspace_bytes(int S, int L, int Hq, int D, int nsplit);
 
 struct EntropyBatch;
+// Whether the logit rows of a bf16 prefix call go with the suffix launch (four
+// waves per row) instead of the context launch (one): where the context is
+// read before one wave is through a row.
+bool rows_with_suffix(const AttnParams &p, const EntropyBatch &e);
 // ent: NULL, or the entropy rows computed in the same launch (rows 16-byte
 // aligned, no workspace): with the own-cache kernel, or with a prefix in the
 // context kernel (p planned with ent_rows = the batch's rows).

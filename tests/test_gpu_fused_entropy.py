@@ -37,6 +37,10 @@ CASES = [
      [(5, 1023, 1024, 2.0, 1.0, True), (3, 5, 8, 1.0, 1.0, False), (2, 8, 8, 0.5, 2.0, True)]),
     ((2, 1, 2, 4, 64, 12, 4, 6, torch.bfloat16), torch.bfloat16, [(7, 50000, 50000, 2.0, 1.0, True)]),
     ((1, 1, 1, 4, 64, 16, 8, 16, torch.float32), torch.float32, [(1, 1024, 1024, 2.0, 1.0, True)]),
+    # 640 units: long rows get a launch of their own, short ones a wave of the attention launch each.
+    ((16, 10, 4, 7, 128, 64, 32, 64, torch.bfloat16), torch.bfloat16, [(6, 152064, 152064, 3.0, 1.0, True)]),
+    ((16, 10, 4, 4, 64, 64, 32, 64, torch.bfloat16), torch.float32,
+     [(5, 1023, 1024, 2.0, 1.0, True), (3, 8, 8, 1.0, 1.0, False)]),
 ]
 
 
@@ -148,6 +152,11 @@ SAMPLE_CASES = [
     ((3, 2, 2, 8, 128, 16, 4, 8, torch.bfloat16), torch.float32,
      [(5, 1023, 1024, 2.0), (3, 5, 8, 1.0), (2, 8, 8, "flat")], (1.0, 64, 1.0, 9, 0)),
     ((1, 1, 1, 4, 64, 16, 8, 16, torch.float32), torch.bfloat16, [(4, 1024, 1024, 2.0)], (0.5, 1, 0.5, 3, 2)),
+    # 640 units: long rows in a launch of their own, short ones in the attention launch.
+    ((16, 10, 4, 7, 128, 64, 32, 64, torch.bfloat16), torch.bfloat16,
+     [(6, 152064, 152064, "boosted"), (3, 30000, 30000, "ties")], (0.8, 20, 0.95, 1234, 7)),
+    ((16, 10, 4, 4, 64, 64, 32, 64, torch.bfloat16), torch.float32,
+     [(5, 1023, 1024, 2.0), (3, 5, 8, 1.0)], (0.8, 50, 0.95, 4, 1)),
 ]
 
 
@@ -230,6 +239,9 @@ PREFIX_CASES = [
     ((8, 2, 1, 2, 8, 128, 2100, 33, torch.bfloat16), torch.bfloat16, [(3, 151936, 151936, "boosted", True)], None),
     ((8, 1, 1, 1, 8, 128, 300, 16, torch.bfloat16), torch.float32, [(4, 5000, 5000, "2.0", False)],
      (0.8, 20, 0.95, 5, 1)),
+    # Rows short enough for the context launch (one wave each), with the sampler.
+    ((6, 3, 2, 2, 6, 64, 513, 20, torch.bfloat16), torch.bfloat16, [(6, 300, 304, "boosted", True)],
+     (0.8, 20, 0.95, 77, 3)),
     # float32 caches: the entropy rows run as a kernel of their own after the attention kernel.
     ((4, 2, 2, 2, 6, 128, 200, 24, torch.float32), torch.float32, [(4, 1024, 1024, "2.0", True)], None),
 ]
@@ -238,7 +250,7 @@ PREFIX_CASES = [
 @pytest.mark.parametrize("ci", range(len(PREFIX_CASES)))
 def test_decode_attn_entropy_with_prefix(ci):
     """kvr_decode_attn_entropy(_sample) with a prefix: the logit rows ride in
-    the context launch. Attention outputs within the helper path's tolerance
+    the context launch, or in the suffix launch where they would outlast it. Attention outputs within the helper path's tolerance
     of the oracle (the split points differ from kvr_decode_attn's, so the
     outputs agree with it to rounding, not bit for bit), the appended suffix
     rows bit for bit, entropies within 1e-4 of the oracle, the detector as
