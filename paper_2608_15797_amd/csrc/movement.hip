@@ -149,16 +149,21 @@ __global__ __launch_bounds__(kThreads) void fork_kernel(ForkParams p, int row_un
   }
 }
 
-// grid (units, chunks): chunk c of unit u copies vectors
+// One workgroup per (unit, chunk): chunk c of unit u copies vectors
 // [c * kUnroll * kThreads, (c + 1) * kUnroll * kThreads) of the unit's T rows.
-__global__ __launch_bounds__(kThreads) void append_kernel(AppendParams p, int row_units) {
-  const int unit = blockIdx.x;  // (s * L + l) * Hkv + h
+// Chunk-fastest, as in the fork, so that the resident workgroups read and
+// write adjacent pieces: append and window scores of 3000 tokens to 16 x 28 x 4
+// units 1.94 -> 1.88 ms against unit-fastest, of 700 tokens 588 -> 577 us, of 16
+// and 100 equal.
+__global__ __launch_bounds__(kThreads) void append_kernel(AppendParams p, int row_units, int chunks) {
+  const int unit = blockIdx.x / chunks;  // (s * L + l) * Hkv + h
+  const int chunk = blockIdx.x - unit * chunks;
   const int s = unit / (p.L * p.Hkv);
   int n = p.len[s];
   n = n < 0 ? 0 : (n > p.cap ? p.cap : n);
   const int rows = p.T < p.cap - n ? p.T : p.cap - n;  // rows that fit
   const int nv = rows * row_units;
-  const int v0 = blockIdx.y * kUnroll * kThreads;
+  const int v0 = chunk * kUnroll * kThreads;
   const int tid = threadIdx.x;
   const size_t row_vec = (size_t)row_units;
   const u32x4 *sk = static_cast<const u32x4 *>(p.k_new) + (size_t)unit * p.T * row_vec;
@@ -182,7 +187,7 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams p, int ro
       __builtin_nontemporal_store(rv[a], dv + i);
     }
   }
-  if (p.pos_new && blockIdx.y == 0) {
+  if (p.pos_new && chunk == 0) {
     int32_t *dp = p.pos + (size_t)unit * p.cap + n;
     const int32_t *sp = p.pos_new + (size_t)s * p.T;
     for (int j = tid; j < rows; j += kThreads) dp[j] = sp[j];
@@ -207,8 +212,8 @@ hipError_t launch_append(const AppendParams &p, hipStream_t stream) {
   const int row_units = p.D * p.esz / 16;
   const long nv = (long)p.T * row_units;
   const int chunks = (int)((nv + kUnroll * kThreads - 1) / (kUnroll * kThreads));
-  hipLaunchKernelGGL(append_kernel, dim3(p.S * p.L * p.Hkv, chunks), dim3(kThreads), 0, stream, p,
-                     row_units);
+  hipLaunchKernelGGL(append_kernel, dim3((unsigned)(p.S * p.L * p.Hkv) * (unsigned)chunks), dim3(kThreads), 0, stream,
+                     p, row_units, chunks);
   return hipGetLastError();
 }
 
