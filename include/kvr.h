@@ -189,6 +189,8 @@ size_t kvr_decode_attn_workspace_size(const kvr_cache *cache, const kvr_prefix *
  *             rows r and the G query heads of KV head h of the probability of
  *             slot j (0 where row r cannot see j). accumulate != 0 adds to the
  *             stored value instead of overwriting. Slots >= len[s] untouched.
+ * bfloat16: a NaN logit counts as no probability, and a row with a logit of
+ * +inf, or without a finite one, adds nothing to any slot.
  * Results are bitwise reproducible (the bf16 kernel adds its float32 sums of
  * at most 16 rows in float64, in a fixed order). Errors: as kvr_decode_attn,
  * and KVR_EUNSUPPORTED when cap exceeds 8192 slots (bf16) or (D + 2 cap) floats

@@ -25,7 +25,9 @@
 //   - No running maximum: a row's exps need no reference as long as its
 //     normaliser stays within 2^-20 .. 2^24, which is tested once per row. A
 //     head with a row outside takes the two passes relative to each row's
-//     maximum, found by a pass of its own.
+//     maximum, found by a pass of its own. There a NaN logit counts as no
+//     probability, and a row with an infinite logit (or none finite) adds
+//     nothing, so neither reaches another key's or row's score.
 // Column sums are float32 over at most 8 rows a lane, then float64 in a
 // fixed order, so the scores are bitwise reproducible and as exact as their
 // float32 result (commit shape 2.7e-8 in the 2-norm against float64; 2.9e-8, but
@@ -159,6 +161,9 @@ constexpr int kFlush = 4;        // blocks of 32 rows between the float32 column
 // (log2), so the float32 exponents lose nothing against a maximum-relative
 // form, and nothing that counts underflows.
 constexpr float kZLow = 0x1p-20f, kZHigh = 0x1p24f;
+// Exponent of an exp relative to a row's maximum: NaN (a NaN logit, or an
+// infinite one less an infinite maximum) and anything as small become 2^-256 = 0.
+__device__ __forceinline__ float rel_exp2(float x) { return fast_exp2(fmaxf(x, -256.0f)); }
 
 template <int D>
 struct WLds {
@@ -411,7 +416,7 @@ struct Window {
       float x = MODE == 2 ? fmaf(a, c, -m[MODE == 2 ? k : 0][i]) : a * c;
       if (!sees) x = kNegInf;
       if (MODE == 1) z[k][i] = fmaxf(z[k][i], x);
-      else z[k][i] += fast_exp2(x);
+      else z[k][i] += MODE == 2 ? rel_exp2(x) : fast_exp2(x);
     };
     // Blocks of keys that every row sees, then the others with the mask.
     const int seen = n - p.nq + 1;
@@ -442,8 +447,13 @@ struct Window {
         if (MODE == 0) bad |= live && !(v[i] >= kZLow && v[i] <= kZHigh);
         if (MODE == 1) v[i] = live && v[i] > kNegInf ? v[i] : 0.f;
         else v[i] = live && v[i] > 0.f ? recip(v[i]) : 0.f;
+        // Relative to this, every exp of a row that adds nothing is 0.
+        if (MODE == 2 && v[i] == 0.f) m[MODE == 2 ? k : 0][i] = -kNegInf;
       }
-      if (r16 == 0) *reinterpret_cast<float4_t *>((MODE == 1 ? lds.g.m : lds.g.f) + at(k)) = v;
+      if (r16 == 0) {
+        *reinterpret_cast<float4_t *>((MODE == 1 ? lds.g.m : lds.g.f) + at(k)) = v;
+        if (MODE == 2) *reinterpret_cast<float4_t *>(lds.g.m + at(k)) = m[MODE == 2 ? k : 0];
+      }
     }
     if (MODE == 0 && bad) lds.bad = 1;
   }
@@ -463,8 +473,8 @@ struct Window {
   }
 
   // Pass 2, over the group's rows with tiles k0 .. k0 + T - 1 of the keys in
-  // the waves' registers: their column sums.
-  template <int T, bool MASK>
+  // the waves' registers: their column sums. REF: relative to the rows' maxima.
+  template <int T, bool MASK, bool REF>
   __device__ __forceinline__ void columns(int row0, int blocks, int k0) const {
     const int gq = lane >> 4, r16 = lane & 15;
     u32x4 kf[T][KS];
@@ -480,12 +490,26 @@ struct Window {
         for (int i = 0; i < 4; i++) {
           float x = fmaf(a[k][i], c, -m);
           if (MASK) x = (wave + kNW * (k0 + k)) * 16 + 4 * gq + i < nr ? x : kNegInf;
-          acc[k][i] = fmaf(fast_exp2(x), f, acc[k][i]);
+          acc[k][i] = fmaf(REF ? rel_exp2(x) : fast_exp2(x), f, acc[k][i]);
         }
       if (h % (2 * kFlush) == 2 * kFlush - 1) flush<T>(acc);
     });
     flush<T>(acc);
     put<T>(k0, p.accumulate != 0 || row0 > 0);
+  }
+
+  template <bool REF>
+  __device__ __forceinline__ void columns_of(int row0, int blocks, int slots, int seen) const {
+#pragma unroll 1
+    for (int k0 = 0; k0 < slots; k0 += kKeyTiles) {
+      const int kt = slots - k0;
+      // Uniform over the workgroup (every wave meets the barriers inside).
+      const bool mask = kNW * (k0 + kKeyTiles) * 16 > seen;
+      if (kt <= 2) fresh().template columns<2, true, REF>(row0, blocks, k0);
+      else if (kt <= 4) fresh().template columns<4, true, REF>(row0, blocks, k0);
+      else if (mask) fresh().template columns<kKeyTiles, true, REF>(row0, blocks, k0);
+      else fresh().template columns<kKeyTiles, false, REF>(row0, blocks, k0);
+    }
   }
 
   __device__ __forceinline__ void two_pass(int slots) const {
@@ -506,16 +530,9 @@ struct Window {
       if (lds.bad) {
         normalise<1>(row0, 2 * blocks);
         normalise<2>(row0, 2 * blocks);
-      }
-#pragma unroll 1
-      for (int k0 = 0; k0 < slots; k0 += kKeyTiles) {
-        const int kt = slots - k0;
-        // Uniform over the workgroup (every wave meets the barriers inside).
-        const bool mask = kNW * (k0 + kKeyTiles) * 16 > seen;
-        if (kt <= 2) fresh().template columns<2, true>(row0, blocks, k0);
-        else if (kt <= 4) fresh().template columns<4, true>(row0, blocks, k0);
-        else if (mask) fresh().template columns<kKeyTiles, true>(row0, blocks, k0);
-        else fresh().template columns<kKeyTiles, false>(row0, blocks, k0);
+        columns_of<true>(row0, blocks, slots, seen);
+      } else {
+        columns_of<false>(row0, blocks, slots, seen);
       }
     }
   }

@@ -527,6 +527,40 @@ def test_accumulate_scores_edges(D, G, nq, lens, std, shift):
     assert torch.equal(again.view(torch.int32), sc.view(torch.int32))
 
 
+@pytest.mark.parametrize("D,G,nq,n", [(128, 7, 32, 297), (64, 2, 16, 97), (128, 4, 40, 640), (128, 7, 32, 997),
+                                      (64, 8, 130, 800)])
+@pytest.mark.parametrize("where,value", [("row", math.nan), ("key", math.nan), ("key", math.inf), ("key", -math.inf),
+                                         ("row", math.inf), ("late key", math.nan), ("late key", math.inf)])
+def test_accumulate_scores_nan_and_inf(D, G, nq, n, where, value):
+    """A NaN logit counts as no probability of its key, and a window row with a
+    logit of +inf (or none finite) adds nothing to any key: one such query row
+    or key leaves the scores that the other rows and keys give, within the
+    tolerance of finite inputs (1e-4). A late key is hidden from the first
+    window rows, which it does not touch."""
+    k = kvr()
+    g = torch.Generator().manual_seed(D + n)
+    K, q = randn((1, 1, 1, n + 3, D), g, torch.bfloat16), randn((1, 1, G, nq, D), g, torch.bfloat16)
+    if where == "row":
+        q[0, 0, 1, nq // 2, 3] = value
+    else:
+        j = 20 if where == "key" else n - nq // 2
+        K[0, 0, 0, j, 4] = value
+    scale = 1.0 / math.sqrt(D)
+    sc = torch.full((1, 1, 1, n + 3), 0.25, device=DEV)
+    say("window scores with", where, value, D, G, nq, n)
+    k.accumulate_scores(k.Cache(K.to(DEV), K.to(DEV), None), torch.tensor([n], dtype=torch.int32, device=DEV), q.to(DEV),
+                        scale, sc, accumulate=False)
+    torch.cuda.synchronize()
+    x = torch.matmul(q[0, 0].double(), K[0, 0, 0, :n].double().T) * scale  # [G, nq, n]
+    late = torch.arange(n)[None, :] >= n - (nq - 1 - torch.arange(nq))[:, None]
+    x = x.masked_fill(late, -math.inf).nan_to_num(nan=-math.inf, posinf=math.inf, neginf=-math.inf)
+    dead = (x == math.inf).any(-1, keepdim=True) | (x == -math.inf).all(-1, keepdim=True)
+    ref = torch.softmax(x.masked_fill(dead, 0.0), -1).masked_fill(dead, 0.0).sum((0, 1))
+    got = sc[0, 0, 0].cpu().double()
+    assert (got[:n] - ref).abs().max() <= 1e-4
+    assert (got[n:] == 0.25).all()
+
+
 # ------------------------------------------------------------ entropy
 
 ENT_CASES = [
