@@ -845,28 +845,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void at
 }
 
 #if !KVR_ATTN_WIDE
-// Own-cache kernel for launches of few units (one layer at a time, few
-// candidates, the suffixes of a few helper contexts): kSplitWaves waves per
-// unit, each with every kSplitWaves-th chunk of 16 keys through a key ring of
-// its own. Bound by the length of a unit's chain (live length, chunks,
-// epilogue) and not by bytes: one wave per unit leaves the chip a wave or two
-// per CU, and a suffix of 512 tokens is 16 chunks one after another. The
-// waves' partial outputs, maxima and sums meet in LDS (each in its own, used
-// up, ring), and a thread finishes 8 columns of a row. MERGE folds in the
-// context kernel's partials there: a thread's share of the first kFastPieces
-// records is loaded before the stream.
+// Suffix kernel of launches of few units (the suffixes of a few helper
+// contexts): kSplitWaves waves per unit, each with every kSplitWaves-th chunk
+// of 16 keys through a key ring of its own. Bound by the length of a unit's
+// chain (live length, chunks, epilogue) and not by bytes: one wave per unit
+// leaves the chip a wave or two per CU, and a suffix of 512 tokens is 16
+// chunks one after another. The waves' partial outputs, maxima and sums meet
+// in LDS (each in its own, used up, ring), and a thread finishes 8 columns of a
+// row and folds in the context kernel's partials: its share of the first
+// kFastPieces records is loaded before the stream.
+// Evicted caches always take the one-wave kernel, so that a sequence's output
+// bits do not depend on how many sequences and layers share its call.
 constexpr int kSplitWaves = 4;
 constexpr int kSplitTiles = 1;
 constexpr int kSplitDepth = 3;
 
 template <int D>
 constexpr size_t split_ring = kl_ring<D, kSplitTiles, kSplitDepth>;  // of one wave
-// Rings, then each wave's row maxima and sums, the rows' merged ones, the new token's logits.
+// Rings, then each wave's row maxima and sums.
 template <int D>
-constexpr size_t split_lds = kSplitWaves * split_ring<D> + (2 * kSplitWaves + 3) * 16 * sizeof(float);
+constexpr size_t split_lds = kSplitWaves * split_ring<D> + 2 * kSplitWaves * 16 * sizeof(float);
 
-template <int D, bool MERGE, int LT>
-__global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(2))) void attn_cache_split_bf16(
+template <int D, int LT>
+__global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(2))) void attn_suffix_split_bf16(
     AttnParams p, EntropyBatch e) {
   constexpr int NW = kSplitWaves, CH = 16 * kSplitTiles, DEPTH = kSplitDepth;
   constexpr int NB = Geo<D>::NB;
@@ -909,8 +910,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
   const bool has_new = p.k_new != nullptr && wave == 0;  // the first wave takes the new token
 
   // As in the one-wave kernel, the loads that do not depend on the live
-  // length go first: the query rows, the new token's rows and, for an evicted
-  // cache, the wave's first chunk (stale rows masked and zeroed below).
+  // length go first: the query rows and the new token's rows.
   short4_t qop[NB];
   load_qop<D>(r16 < G ? static_cast<const bf16_t *>(p.q) + (qrow0 + r16) * D : nullptr, g4, qop);
   KVChunk<D, 1> cn;
@@ -921,10 +921,6 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
   char *kring = reinterpret_cast<char *>(smem) + wave * split_ring<D>;
   const KLOffsets<D, kSplitTiles> kloff(lane);
   const int k0 = wave * CH;
-  if constexpr (!MERGE) {
-    const int first = p.cap < k0 + CH ? p.cap : k0 + CH;
-    load_chunk_lds<D, kSplitTiles>(vring[0], kring, Kc, Vc, first, k0, kloff);
-  }
 
   int n = p.len[s];
   n = n < 0 ? 0 : (n > p.cap ? p.cap : n);
@@ -933,40 +929,29 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
   const int32_t npos = put_pos ? p.new_pos[s] : 0;
   const int ncache = append ? n - 1 : n;
 
-  // This thread's 8 output columns (threads past G * D / 8: none) and, with
-  // MERGE, its share of the row's first context partials.
+  // This thread's 8 output columns (threads past G * D / 8: none) and its
+  // share of the row's first context partials.
   const int orow = tid / (D / 8), ocol = 8 * (tid % (D / 8));
   constexpr int RF = kRecFloats<D>;
-  int npieces = 0;
   const size_t rstride = (size_t)p.S * p.L * p.Hq * RF;
-  const float *rbase = nullptr;
+  const long ug = ((long)((s / p.C) * p.L + l) * p.Hkv + h) * p.pitch;
+  const int npieces = (int)((ug + p.plen - 1) / p.span - ug / p.span) + 1;
+  const float *rbase = p.ws + (qrow0 + orow) * RF;
   float2_t pms[kFastPieces];
   u32x4 phv[kFastPieces];
-  if constexpr (MERGE) {
-    const long ug = ((long)((s / p.C) * p.L + l) * p.Hkv + h) * p.pitch;
-    npieces = (int)((ug + p.plen - 1) / p.span - ug / p.span) + 1;
-    rbase = p.ws + (qrow0 + orow) * RF;
 #pragma unroll
-    for (int k = 0; k < kFastPieces; k++) {
-      pms[k] = float2_t{kNegInf, 0.f};
-      phv[k] = u32x4{0u, 0u, 0u, 0u};
-      if (orow < G && k < npieces) {
-        pms[k] = *reinterpret_cast<const float2_t *>(rbase + k * rstride);
-        phv[k] = *reinterpret_cast<const u32x4 *>(rbase + k * rstride + 4 + ocol / 2);
-      }
+  for (int k = 0; k < kFastPieces; k++) {
+    pms[k] = float2_t{kNegInf, 0.f};
+    phv[k] = u32x4{0u, 0u, 0u, 0u};
+    if (orow < G && k < npieces) {
+      pms[k] = *reinterpret_cast<const float2_t *>(rbase + k * rstride);
+      phv[k] = *reinterpret_cast<const u32x4 *>(rbase + k * rstride + 4 + ocol / 2);
     }
-    load_chunk_lds<D, kSplitTiles>(vring[0], kring, Kc, Vc, ncache, k0, kloff);
   }
+  load_chunk_lds<D, kSplitTiles>(vring[0], kring, Kc, Vc, ncache, k0, kloff);
 
-  // Observation-window step of this sequence?
-  const int wstart = p.B + p.buffer + 2 - p.W;
-  const bool win = !MERGE && p.scores != nullptr && n >= wstart;
-  const int ldx = (p.cap + 63) & ~63;
   float *wm = smem + NW * split_ring<D> / sizeof(float);  // [NW][16] the waves' row maxima
   float *wz = wm + NW * 16;                               // [NW][16] and sums
-  float *stat = wz + NW * 16;                             // [16] max, [16] 1/sum
-  float *xn = stat + 32;                                  // [16] the new token's logits
-  float *xs = xn + 16;                                    // [G][ldx] logits of window steps
 
   const float sl2 = p.scale * kLog2e;
   RowState st{kNegInf, 0.0f};
@@ -975,32 +960,11 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
   for (int b = 0; b < NB; b++) o[b] = float4_t{0.f, 0.f, 0.f, 0.f};
 
   auto process = [&](VChunk<D, kSplitTiles> &c, const char *kslot, int c0) {
-    if (!MERGE && c0 == k0 && ncache < c0 + CH) {
-      // The first chunk was read before the live length was known.
-#pragma unroll
-      for (int cc = 0; cc < 4; cc++)
-        if (c0 + 4 * g4 + cc >= ncache)
-#pragma unroll
-          for (int w = 0; w < Geo<D>::VW; w++) c.v[0][cc][w] = 0u;
-    }
     float x[1][4];
     chunk_logits_lds<D, 1>(kslot, qop, x, c0, ncache, r16, g4, sl2, c0 + CH > ncache);
-    if (win && r16 < G)
-      *reinterpret_cast<float4_t *>(xs + r16 * ldx + c0 + 4 * g4) = float4_t{x[0][0], x[0][1], x[0][2], x[0][3]};
     softmax_pv<D, 1, true>(x, st, o, c.v, g4);
   };
 
-  // Stored scores of window steps that accumulate, prefetched.
-  constexpr int PRE = 2;  // per thread (slots < 512)
-  const bool accumulate = win && n != wstart;
-  float old[PRE];
-  float *sc = win ? p.scores + (size_t)unit * p.cap : nullptr;
-  if (accumulate) {
-    const rsrc_t Sr = make_rsrc(sc, (uint32_t)(n - 1) * 4u);
-#pragma unroll
-    for (int k = 0; k < PRE; k++)
-      old[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(Sr, (uint32_t)(tid + NT * k) * 4u, 0, 0));
-  }
   auto new_token = [&]() {
     if (has_new && append) {
       if (r16 == 0) {
@@ -1020,7 +984,6 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
       if (put_pos && lane == 16) __builtin_nontemporal_store(npos, p.pos + (size_t)unit * p.cap + n - 1);
       float x[1][4];
       chunk_logits<D, 1>(cn, qop, x, 0, 1, g4, sl2, true);
-      if (g4 == 0) xn[r16] = x[0][0];
       softmax_pv<D, 1, true>(x, st, o, cn.v, g4);
     }
   };
@@ -1051,10 +1014,8 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
     float M = kNegInf;
 #pragma unroll
     for (int w = 0; w < NW; w++) M = fmaxf(M, wm[w * 16 + orow]);
-    if constexpr (MERGE) {
 #pragma unroll
-      for (int k = 0; k < kFastPieces; k++) M = fmaxf(M, pms[k].x);
-    }
+    for (int k = 0; k < kFastPieces; k++) M = fmaxf(M, pms[k].x);
     float zs = 0.f;
     float4_t a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1067,65 +1028,41 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
       a += *reinterpret_cast<const float4_t *>(r) * f;
       b += *reinterpret_cast<const float4_t *>(r + 4) * f;
     }
-    if constexpr (MERGE) {
-      // Log-sum-exp merge with the context partials (max, sum, -, -, o / sum).
-      auto fold = [&](float2_t ms, u32x4 hv) {
-        const float f = ms.x == kNegInf ? 0.f : ms.y * fast_exp2(ms.x - M);
-        zs += f;
-        a += float4_t{f16_lo(hv.x), f16_hi(hv.x), f16_lo(hv.y), f16_hi(hv.y)} * f;
-        b += float4_t{f16_lo(hv.z), f16_hi(hv.z), f16_lo(hv.w), f16_hi(hv.w)} * f;
-      };
+    // Log-sum-exp merge with the context partials (max, sum, -, -, o / sum).
+    auto fold = [&](float2_t ms, u32x4 hv) {
+      const float f = ms.x == kNegInf ? 0.f : ms.y * fast_exp2(ms.x - M);
+      zs += f;
+      a += float4_t{f16_lo(hv.x), f16_hi(hv.x), f16_lo(hv.y), f16_hi(hv.y)} * f;
+      b += float4_t{f16_lo(hv.z), f16_hi(hv.z), f16_lo(hv.w), f16_hi(hv.w)} * f;
+    };
+#pragma unroll
+    for (int k = 0; k < kFastPieces; k++) fold(pms[k], phv[k]);
+    // Further records in batches, each batch's loads issued together.
+    for (int k0 = kFastPieces; k0 < npieces; k0 += kFastPieces) {
+      float Mb = M;
+#pragma unroll
+      for (int k = 0; k < kFastPieces; k++) {
+        const float *r = rbase + (k0 + k < npieces ? k0 + k : k0) * rstride;
+        pms[k] = *reinterpret_cast<const float2_t *>(r);
+        phv[k] = *reinterpret_cast<const u32x4 *>(r + 4 + ocol / 2);
+      }
+#pragma unroll
+      for (int k = 0; k < kFastPieces; k++) {
+        if (k0 + k >= npieces) pms[k] = float2_t{kNegInf, 0.f};
+        Mb = fmaxf(Mb, pms[k].x);
+      }
+      const float f = M == kNegInf ? 0.f : fast_exp2(M - Mb);
+      zs *= f;
+      a *= f;
+      b *= f;
+      M = Mb;
 #pragma unroll
       for (int k = 0; k < kFastPieces; k++) fold(pms[k], phv[k]);
-      // Further records in batches, each batch's loads issued together.
-      for (int k0 = kFastPieces; k0 < npieces; k0 += kFastPieces) {
-        float Mb = M;
-#pragma unroll
-        for (int k = 0; k < kFastPieces; k++) {
-          const float *r = rbase + (k0 + k < npieces ? k0 + k : k0) * rstride;
-          pms[k] = *reinterpret_cast<const float2_t *>(r);
-          phv[k] = *reinterpret_cast<const u32x4 *>(r + 4 + ocol / 2);
-        }
-#pragma unroll
-        for (int k = 0; k < kFastPieces; k++) {
-          if (k0 + k >= npieces) pms[k] = float2_t{kNegInf, 0.f};
-          Mb = fmaxf(Mb, pms[k].x);
-        }
-        const float f = M == kNegInf ? 0.f : fast_exp2(M - Mb);
-        zs *= f;
-        a *= f;
-        b *= f;
-        M = Mb;
-#pragma unroll
-        for (int k = 0; k < kFastPieces; k++) fold(pms[k], phv[k]);
-      }
     }
     const float inv = 1.0f / zs;
-    if (win && ocol == 0) {
-      stat[orow] = M;
-      stat[16 + orow] = inv;
-    }
     __builtin_nontemporal_store(u32x4{pack_bf16x2(a[0] * inv, a[1] * inv), pack_bf16x2(a[2] * inv, a[3] * inv),
                                       pack_bf16x2(b[0] * inv, b[1] * inv), pack_bf16x2(b[2] * inv, b[3] * inv)},
                                 reinterpret_cast<u32x4 *>(static_cast<bf16_t *>(p.out) + (qrow0 + orow) * D + ocol));
-  }
-  if constexpr (!MERGE) {
-    if (win) {
-      __syncthreads();
-      auto mass = [&](int j) {
-        float r = 0.0f;
-        for (int g = 0; g < G; g++)
-          r += fast_exp2((append && j == n - 1 ? xn[g] : xs[g * ldx + j]) - stat[g]) * stat[16 + g];
-        return r;
-      };
-#pragma unroll
-      for (int k = 0; k < PRE; k++) {
-        const int j = tid + NT * k;
-        if (j < n) __builtin_nontemporal_store((accumulate && j < n - 1) ? old[k] + mass(j) : mass(j), sc + j);
-      }
-      for (int j = tid + NT * PRE; j < n; j += NT)
-        __builtin_nontemporal_store((accumulate && j < n - 1) ? sc[j] + mass(j) : mass(j), sc + j);
-    }
   }
 }
 #endif  // !KVR_ATTN_WIDE
@@ -1537,13 +1474,9 @@ void launch_prefix(const AttnParams &p, const EntropyBatch *e, hipStream_t strea
 }
 
 #if !KVR_ATTN_WIDE
-// Four waves per unit (attn_cache_split_bf16) where the units are few: one per
-// CU, two where a wave has more chunks than its ring, eight suffixes per CU.
-// Measured (7B heads, us, one wave against four): 256 units of 98-129 tokens
-// 7.6 / 6.2, of 129-257 11.2 / 7.5; 512 units 8.4 / 8.4 and 12.4 / 11.2; 1024
-// units 12.0 / 15.4 and 20.4 / 20.3. Suffixes of 1-512 tokens behind contexts:
+// Four waves per suffix (attn_suffix_split_bf16) where the units are few.
+// Measured, suffixes of 1-512 tokens behind contexts against one wave each:
 // 448 units 12 us less, 1792 5 us less; 3584 of 1-64 tokens 13 us more.
-constexpr long kSplitUnits = 256, kSplitUnitsLong = 512;
 constexpr long kSplitSuffixUnits = 2048;
 
 // A logit row takes one wave about as long as the chip needs for this many
@@ -1592,28 +1525,21 @@ void launch_rows(const EntropyBatch &e, hipStream_t stream) {
   }
 }
 
-// The same with and without logit rows, whose call promises the same bits.
+// The suffix kernel of few units, rows as in launch_own.
 template <int D>
-bool split_own(const AttnParams &p, size_t logits) {
-  const long units = (long)p.S * p.L * p.Hkv;
-  return split_lds<D> + logits <= kMaxLds &&
-         (units <= kSplitUnits || (units <= kSplitUnitsLong && p.cap > 16 * kSplitTiles * kSplitDepth * kSplitWaves));
-}
-
-// The kernel of few units, rows as in launch_own.
-template <int D, bool MERGE>
-void launch_split(const AttnParams &p, const EntropyBatch *e, size_t lds, hipStream_t stream) {
+void launch_suffix_split(const AttnParams &p, const EntropyBatch *e, hipStream_t stream) {
   const int rows = e ? e->row0[e->nsets] : 0;
   const dim3 grid(rows + p.S * p.L * p.Hkv), block(64 * kSplitWaves);
+  const size_t lds = split_lds<D>;
   const EntropyBatch none{};
   const bool f32 = e && e->set[0].dtype == 0;
   const bool sample = e && e->set[0].top_k > 0;
   static_assert(split_lds<64> >= kSampleGroupLds<kSplitWaves>, "the rows' candidate buffers fit");
-  if (!e) hipLaunchKernelGGL((attn_cache_split_bf16<D, MERGE, 0>), grid, block, lds, stream, p, none);
-  else if (sample && f32) hipLaunchKernelGGL((attn_cache_split_bf16<D, MERGE, 4>), grid, block, lds, stream, p, *e);
-  else if (sample) hipLaunchKernelGGL((attn_cache_split_bf16<D, MERGE, 3>), grid, block, lds, stream, p, *e);
-  else if (f32) hipLaunchKernelGGL((attn_cache_split_bf16<D, MERGE, 2>), grid, block, lds, stream, p, *e);
-  else hipLaunchKernelGGL((attn_cache_split_bf16<D, MERGE, 1>), grid, block, lds, stream, p, *e);
+  if (!e) hipLaunchKernelGGL((attn_suffix_split_bf16<D, 0>), grid, block, lds, stream, p, none);
+  else if (sample && f32) hipLaunchKernelGGL((attn_suffix_split_bf16<D, 4>), grid, block, lds, stream, p, *e);
+  else if (sample) hipLaunchKernelGGL((attn_suffix_split_bf16<D, 3>), grid, block, lds, stream, p, *e);
+  else if (f32) hipLaunchKernelGGL((attn_suffix_split_bf16<D, 2>), grid, block, lds, stream, p, *e);
+  else hipLaunchKernelGGL((attn_suffix_split_bf16<D, 1>), grid, block, lds, stream, p, *e);
 }
 
 // The evicted-cache kernel with the entropy rows of `e` (nullptr: none) in
@@ -1658,14 +1584,11 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
     const size_t logits = p.scores ? ((size_t)p.G * ((p.cap + 63) & ~63) + 32) * sizeof(float) : 0;
     const size_t lds_min = D == 128 ? kBaseLdsFloor : 0;
     constexpr size_t ring = kl_ring<D, kKlTiles, kKlDepth>;
-    const bool split = split_own<D>(p, logits);
-    if (ent && !split && rows_outlast(*ent, (double)units.x * p.cap * (4 * D), kOwnShare)) {
+    if (ent && rows_outlast(*ent, (double)units.x * p.cap * (4 * D), kOwnShare)) {
       launch_rows(*ent, stream);
       ent = nullptr;
     }
-    if (split) {
-      launch_split<D, false>(p, ent, split_lds<D> + logits, stream);
-    } else if (ring + logits <= kMaxLds) {
+    if (ring + logits <= kMaxLds) {
       // Key rows through the LDS ring. No floor here: with the keys in LDS,
       // 7-8 workgroups per CU (registers: 172) measured 1-1.5% faster than the
       // 6 of a 26 KiB floor on the 7B shapes and equal on the 72B shape.
@@ -1691,7 +1614,7 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
   const size_t pre = (size_t)p.merge_pf * p.merge_blk * sizeof(float);
   constexpr size_t ring = kl_ring<D, kKlTiles, kKlDepth>;
   if ((long)p.S * p.L * p.Hkv <= kSplitSuffixUnits)
-    launch_split<D, true>(p, late, split_lds<D>, stream);
+    launch_suffix_split<D>(p, late, stream);
   else if constexpr (kSuffixKl)
     hipLaunchKernelGGL((attn_cache_bf16<D, true, kKlTiles, kKlDepth, true>), units, dim3(64), ring + pre, stream, p,
                        EntropyBatch{});

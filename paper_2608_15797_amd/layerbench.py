@@ -11,9 +11,8 @@ model keeps them), issued eagerly and as one captured HIP graph per step, next
 to the layer-batched call. Every live length is the mean of the eviction
 cycle, B + (buffer + 2) / 2, and the new token is appended as in decode (the
 same slot each repetition). Before timing, the per-layer outputs are checked
-bit for bit against the batched call's (equal where both launches take the
-same kernel; launches of few (sequence, layer, KV head) units take one with
-four waves per unit, whose sums differ in the last bits), and three graph replays, with
+bit for bit against the batched call's (the kernel computes each (sequence,
+layer, KV head) unit the same way in both), and three graph replays, with
 eager launches and synchronisations between them, against the eager ones.
 Prints one JSON line.
 """

@@ -55,9 +55,9 @@ CALL_KERNELS = {
     # and with them (1: bf16 logits, 2: float32 logits).
     "base_attn": (r"attn_cache_bf16<\d+, false, \d+, \d+, (true|false), 0>",),
     "base_attn_entropy": (r"attn_cache_bf16<\d+, false, \d+, \d+, (true|false), [12]>",),
-    "helper_attn": (r"attn_prefix_bf16<", r"attn_cache(_split)?_bf16<\d+, true"),
+    "helper_attn": (r"attn_prefix_bf16<", r"attn_(cache_bf16<\d+, true|suffix_split_bf16<)"),
     # The context kernel with the logit rows in front, then the suffix kernel.
-    "helper_attn_entropy": (r"attn_prefix_rows_bf16<", r"attn_cache(_split)?_bf16<\d+, true"),
+    "helper_attn_entropy": (r"attn_prefix_rows_bf16<", r"attn_(cache_bf16<\d+, true|suffix_split_bf16<)"),
     "evict": (r"evict_topb_kernel",),
     "entropy": (r"entropy_kernel<", r"?entropy_merge"),
 }
@@ -145,7 +145,7 @@ def window_stats(db: str, window) -> list[str]:
     return out
 
 
-SUFFIX_KERNEL = re.compile(r"attn_cache(_split)?_bf16<\d+, true")
+SUFFIX_KERNEL = re.compile(r"attn_(cache_bf16<\d+, true|suffix_split_bf16<)")
 
 
 def suffix_fit(db: str, bench_json: str, window=(0, 1)) -> list[str]:
