@@ -1279,8 +1279,8 @@ __global__ __launch_bounds__(64) void attn_prefix_rows_bf16(AttnParams p, Entrop
 // read again for every head) took 1640 us for 8 x 28 x 4 units of 129-257
 // tokens (G = 7, D = 128); this takes 46 us
 // (184 MB, 4.0 TB/s).
-// LDS: q rows [G][D], logits [G][ld], stats [2][16]; the groups' sums
-// [4][G][D] over the first two once they are used.
+// LDS: q rows [G][D], logits [G][ld]; the groups' sums [4][G][D] over both
+// once they are used.
 constexpr int kF32Threads = 256;
 
 template <int CTRL>
@@ -1289,7 +1289,7 @@ __device__ __forceinline__ float add_dpp(float v) {
 }
 
 template <int D, int GM>
-__global__ __launch_bounds__(kF32Threads) void attn_f32(AttnParams p, int ld, int lds_stat) {
+__global__ __launch_bounds__(kF32Threads) void attn_f32(AttnParams p, int ld) {
   extern __shared__ __align__(16) float smem[];
   constexpr int NW = kF32Threads / kWave;
   const int unit = blockIdx.x;
@@ -1331,7 +1331,6 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32(AttnParams p, int ld, in
   };
   float *qs = smem;
   float *xs = smem + G * D;
-  float *stat = smem + lds_stat;
   const size_t qrow0 = ((size_t)s * p.L + l) * p.Hq + h * G;
   for (int e = tid; e < G * D; e += kF32Threads) qs[e] = static_cast<const float *>(p.q)[qrow0 * D + e];
   __syncthreads();
@@ -1372,7 +1371,8 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32(AttnParams p, int ld, in
   }
   __syncthreads();
 
-  // Softmax numerators in place; 1 / sum of each head in stat.
+  // Probabilities in place. Normalised here, so that the output sums stay
+  // within the value rows' range however large those are.
   for (int g = wave; g < G; g += NW) {
     float m = kNegInf;
     for (int j = lane; j < nt; j += kWave) m = fmaxf(m, xs[g * ld + j]);
@@ -1383,8 +1383,8 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32(AttnParams p, int ld, in
       xs[g * ld + j] = e;
       z += e;
     }
-    z = wave_sum(z);
-    if (lane == 0) stat[g] = nt > 0 ? 1.0f / z : 0.f;
+    const float iz = 1.0f / wave_sum(z);
+    for (int j = lane; j < nt; j += kWave) xs[g * ld + j] *= iz;
   }
   __syncthreads();
 
@@ -1395,7 +1395,7 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32(AttnParams p, int ld, in
     float *sc = p.scores + (size_t)unit * p.cap;
     for (int j = tid; j < n; j += kF32Threads) {
       float r = 0.f;
-      for (int g = 0; g < G; g++) r += xs[g * ld + j] * stat[g];
+      for (int g = 0; g < G; g++) r += xs[g * ld + j];
       sc[j] = (first || j == n - 1) ? r : sc[j] + r;
     }
   }
@@ -1449,7 +1449,7 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32(AttnParams p, int ld, in
     float v = smem[e];
 #pragma unroll
     for (int w = 1; w < NW; w++) v += smem[w * G * D + e];
-    out[e] = v * stat[e / D];
+    out[e] = v;
   }
 }
 #endif  // !KVR_ATTN_WIDE
@@ -1631,13 +1631,13 @@ void launch_f32(const AttnParams &p, hipStream_t stream) {
   const size_t nt = (size_t)(p.P > 0 ? p.plen : 0) + p.cap;
   size_t ld = (nt + 3) / 4 * 4;
   if ((p.G * (D + ld) + 32) * sizeof(float) > kMaxLds) ld = nt;
-  size_t stat = p.G * (D + ld);
-  if (stat < (size_t)4 * p.G * D) stat = (size_t)4 * p.G * D;
-  const size_t lds = (stat + 32) * sizeof(float);
+  size_t lds = p.G * (D + ld);
+  if (lds < (size_t)4 * p.G * D) lds = (size_t)4 * p.G * D;
+  lds *= sizeof(float);
   const dim3 grid(p.S * p.L * p.Hkv);
-  if (p.G <= 4) hipLaunchKernelGGL((attn_f32<D, 4>), grid, dim3(kF32Threads), lds, stream, p, (int)ld, (int)stat);
-  else if (p.G <= 8) hipLaunchKernelGGL((attn_f32<D, 8>), grid, dim3(kF32Threads), lds, stream, p, (int)ld, (int)stat);
-  else hipLaunchKernelGGL((attn_f32<D, 16>), grid, dim3(kF32Threads), lds, stream, p, (int)ld, (int)stat);
+  if (p.G <= 4) hipLaunchKernelGGL((attn_f32<D, 4>), grid, dim3(kF32Threads), lds, stream, p, (int)ld);
+  else if (p.G <= 8) hipLaunchKernelGGL((attn_f32<D, 8>), grid, dim3(kF32Threads), lds, stream, p, (int)ld);
+  else hipLaunchKernelGGL((attn_f32<D, 16>), grid, dim3(kF32Threads), lds, stream, p, (int)ld);
 }
 #endif  // !KVR_ATTN_WIDE
 

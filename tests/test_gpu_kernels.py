@@ -236,6 +236,25 @@ def test_decode_attn_prefix_f32_shapes(case):
     test_decode_attn_prefix(case)
 
 
+@pytest.mark.parametrize("D,G,n", [(128, 7, 200), (64, 2, 33)])
+def test_decode_attn_f32_large_values(D, G, n):
+    """Value rows near the largest float32: an output is an average of them, so
+    it stays finite and within the float32 tolerance of the rows' size."""
+    k = kvr()
+    g = torch.Generator().manual_seed(D)
+    K, q = randn((2, 1, 1, n, D), g, torch.float32), randn((2, 1, G, D), g, torch.float32)
+    V = (torch.rand((2, 1, 1, n, D), generator=g) + 2.0) * 1e38
+    out = torch.empty((2, 1, G, D), device=DEV)
+    scale = 1.0 / math.sqrt(D)
+    say("large values", D, G, n)
+    k.decode_attn(k.Cache(K.to(DEV), V.to(DEV), None), torch.full((2,), n, dtype=torch.int32, device=DEV), q.to(DEV), out,
+                  scale)
+    torch.cuda.synchronize()
+    p = torch.softmax((q.double().view(2, 1, 1, G, D) @ K.double().transpose(-1, -2)) * scale, -1)
+    ref = (p @ V.double()).view(2, 1, G, D).numpy()
+    assert rowwise_rel_err(as_f64(out), ref).max() <= TOL[torch.float32]
+
+
 # Work plans of the context: spans over several units (more units than waves fit), spans that cross a unit's end on a
 # full chip, and pieces of a unit's own (odd lengths, more than the records of one batch; one and four waves per suffix).
 @pytest.mark.parametrize("case", [
