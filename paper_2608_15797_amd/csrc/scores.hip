@@ -23,11 +23,15 @@
 //     in registers and the rows streaming (column sums): 3.5 ms against 6.2
 //     on 4096 keys.
 //   - No running maximum: a row's exps need no reference as long as its
-//     normaliser stays within 2^-20 .. 2^24, which is tested once per row. A
-//     head with a row outside takes the two passes relative to each row's
-//     maximum, found by a pass of its own. There a NaN logit counts as no
-//     probability, and a row with an infinite logit (or none finite) adds
-//     nothing, so neither reaches another key's or row's score.
+//     normaliser stays within 2^-80 .. 2^100, which is tested once per row. In
+//     one pass a head with a row outside is done again with the rows' maxima
+//     taken first; in two passes a group of rows with one outside is redone with
+//     references that trail each lane's maximum. Measured with queries of
+//     standard deviation 1 and 8 / 16 to 256 / 64 in one query head of 7: commit
+//     shape 0.45 / 0.67-0.82 / 0.98 ms, 4096 keys 3.5 / 5.5-5.9 / 4.9; two passes
+//     with an online maximum throughout take 1.04-1.16 and 6.3-6.8. There a NaN
+//     logit counts as no probability, and a row with an infinite logit (or
+//     none finite) adds nothing, so neither reaches another key's or row's score.
 // Column sums are float32 over at most 8 rows a lane, then float64 in a
 // fixed order, so the scores are bitwise reproducible and as exact as their
 // float32 result (commit shape 2.7e-8 in the 2-norm against float64; 2.9e-8, but
@@ -144,12 +148,16 @@ __device__ __forceinline__ float reduce16(float v) {
   return op(v, dpp<kMirror>(v));
 }
 
-// Sum of the lanes l, l^16, l^32, l^48, in every one of them.
-__device__ __forceinline__ float sum_groups(float v) {
+// Sum (or maximum) of the lanes l, l^16, l^32, l^48, in every one of them.
+template <bool MAX>
+__device__ __forceinline__ float reduce_groups(float v) {
+  auto op = [](uint32_t a, uint32_t b) {
+    return MAX ? fmaxf(__uint_as_float(a), __uint_as_float(b)) : __uint_as_float(a) + __uint_as_float(b);
+  };
   const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  v = op(a[0], a[1]);
   const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  return op(b[0], b[1]);
 }
 constexpr int kNW = 8;           // waves per workgroup
 constexpr int kKeyTiles = 6;     // 16-key tiles a wave holds at once
@@ -157,12 +165,16 @@ constexpr int kRowTiles = 7;     // 16-row tiles a wave holds at once (pass 1 of
 constexpr int kRG = kNW * kRowTiles * 16;  // window rows per group (two passes)
 constexpr int kFlush = 4;        // blocks of 32 rows between the float32 column sums' flushes
 // A row's exponentials are taken without a reference while its normaliser
-// lies in this range: its largest logit is then between about -30 and 24
-// (log2), so the float32 exponents lose nothing against a maximum-relative
-// form, and nothing that counts underflows.
-constexpr float kZLow = 0x1p-20f, kZHigh = 0x1p24f;
+// lies in this range: its largest logit is then between about -92 and 100
+// (log2), nothing overflows, and the terms that underflow (below 2^-126) are
+// less than 2^-33 of the normaliser together. What a logit's own rounding
+// costs is the matrix product's error again: at logits of standard deviation 8
+// the scores' error in the 2-norm is 2.8e-7 so, 2.6e-7 relative to maxima.
+constexpr float kZLow = 0x1p-80f, kZHigh = 0x1p100f;
+constexpr int kProbe = 8;  // blocks of 32 keys after which a group of rows that already left the range stops
 // Exponent of an exp relative to a row's maximum: NaN (a NaN logit, or an
 // infinite one less an infinite maximum) and anything as small become 2^-256 = 0.
+// A row that adds nothing takes +inf for its maximum.
 __device__ __forceinline__ float rel_exp2(float x) { return fast_exp2(fmaxf(x, -256.0f)); }
 
 template <int D>
@@ -309,71 +321,139 @@ struct Window {
     return rho < R ? n - late : 0;
   }
 
+  // A row's value from the 32 partial ones that the waves left in lds.z[buf]:
+  // this lane takes 8 of them, then the four groups of lanes meet.
+  template <bool MAX>
+  __device__ __forceinline__ float exchange(int buf, int row) const {
+    const float *zr = lds.z[buf][row] + 8 * (lane >> 4);
+    const float4_t a = *reinterpret_cast<const float4_t *>(zr), b = *reinterpret_cast<const float4_t *>(zr + 4);
+    auto op = [](float x, float y) { return MAX ? fmaxf(x, y) : x + y; };
+    return reduce_groups<MAX>(op(op(op(a[0], a[1]), op(a[2], a[3])), op(op(b[0], b[1]), op(b[2], b[3]))));
+  }
+
   // One pass: every key of the head in the waves' registers, the window rows
   // streaming. Per block of 32 rows the waves exchange their partial
   // normalisers through LDS and add the probabilities, each formed once, to
   // the column sums. The last MS tiles may hold keys a row does not see.
-  // False, with nothing written, where a row leaves the range of the
-  // reference-free form.
+  // A head with a row outside the range of the reference-free form is done
+  // again with the rows' maxima taken before the exps (one barrier and a
+  // maximum per logit more). The test comes after 4, 16, 64 ... blocks: after
+  // every one, or with the flush, it costs each head 3 to 5%.
   template <int T, int MS>
-  __device__ __forceinline__ bool one_pass() const {
+  __device__ __forceinline__ void one_pass() const {
     const int gq = lane >> 4, r16 = lane & 15;
     u32x4 kf[T][KS];
     load_tiles<T>(kf, kr, 0, 0);
     float4_t acc[T];
     clear<T>(acc);
     const int blocks = (R + 31) / 32;
-    bool bad = false;
+    auto sees = [&](int k, int i, int nr) { return k < T - MS || (wave + kNW * k) * 16 + 4 * gq + i < nr; };
+    auto add = [&](const float4_t (&v)[2][T], const float (&f)[2]) {
+#pragma unroll
+      for (int b = 0; b < 2; b++)
+#pragma unroll
+        for (int k = 0; k < T; k++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) acc[k][i] = fmaf(v[b][k][i], f[b], acc[k][i]);
+    };
     issue(qr, 0, 0);
     wait_vm<0>();
     bar();
+    bool bad = false;
+    int blk = 0;
 #pragma unroll 1
-    for (int blk = 0; blk < blocks; blk++) {
-      issue(qr, (blk + 1) * 32, (blk + 1) & 1);  // past the last row: zeros, no memory traffic
-      float4_t x[2][T];
-      int nr[2];
+    for (int stop = blocks < kFlush ? blocks : kFlush;; stop = 4 * stop < blocks ? 4 * stop : blocks) {
+#pragma unroll 1
+      for (; blk < stop; blk++) {
+        issue(qr, (blk + 1) * 32, (blk + 1) & 1);  // past the last row: zeros, no memory traffic
+        float4_t x[2][T];
+        int nr[2];
 #pragma unroll
-      for (int b = 0; b < 2; b++) {
-        nr[b] = visible(blk * 32 + 16 * b + r16);
-        products<T>(kf, blk & 1, b, x[b]);
+        for (int b = 0; b < 2; b++) {
+          nr[b] = visible(blk * 32 + 16 * b + r16);
+          products<T>(kf, blk & 1, b, x[b]);
+        }
+#pragma unroll
+        for (int b = 0; b < 2; b++) {
+          float4_t z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int k = 0; k < T; k++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+              const float v = fast_exp2(x[b][k][i] * c);
+              x[b][k][i] = sees(k, i, nr[b]) ? v : 0.f;
+              z[i] += x[b][k][i];
+            }
+          lds.z[blk & 1][16 * b + r16][4 * wave + gq] = (z[0] + z[1]) + (z[2] + z[3]);
+        }
+        wait_vm<0>();
+        bar();
+        float f[2];
+#pragma unroll
+        for (int b = 0; b < 2; b++) {
+          const float Z = exchange<false>(blk & 1, 16 * b + r16);
+          bad |= nr[b] > 0 && !(Z >= kZLow && Z <= kZHigh);
+          f[b] = nr[b] > 0 ? recip(Z) : 0.f;
+        }
+        add(x, f);
+        if (blk % kFlush == kFlush - 1) flush<T>(acc);
       }
-#pragma unroll
-      for (int b = 0; b < 2; b++) {
-        float4_t z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int k = 0; k < T; k++)
-#pragma unroll
-          for (int i = 0; i < 4; i++) {
-            float v = fast_exp2(x[b][k][i] * c);
-            if (k >= T - MS) v = (wave + kNW * k) * 16 + 4 * gq + i < nr[b] ? v : 0.f;
-            x[b][k][i] = v;
-            z[i] += v;
-          }
-        lds.z[blk & 1][16 * b + r16][4 * wave + gq] = (z[0] + z[1]) + (z[2] + z[3]);
-      }
+      // The waves hold the same normalisers, so they agree.
+      if (__builtin_amdgcn_ballot_w64(bad) != 0 || stop == blocks) break;
+    }
+    if (__builtin_amdgcn_ballot_w64(bad) != 0) {
+      blk = 0;
+      clear<T>(acc);
+      bar();  // every wave's reads of the ring and the normalisers are done
+      issue(qr, blk * 32, blk & 1);
       wait_vm<0>();
       bar();
+#pragma unroll 1
+      for (; blk < blocks; blk++) {
+        issue(qr, (blk + 1) * 32, (blk + 1) & 1);
+        float4_t x[2][T];
+        int nr[2];
 #pragma unroll
-      for (int b = 0; b < 2; b++) {
-        // This lane adds 8 of the row's 32 partials, then the four groups.
-        const float *zr = lds.z[blk & 1][16 * b + r16] + 8 * gq;
-        const float4_t za = *reinterpret_cast<const float4_t *>(zr), zb = *reinterpret_cast<const float4_t *>(zr + 4);
-        const float Z = sum_groups(((za[0] + za[1]) + (za[2] + za[3])) + ((zb[0] + zb[1]) + (zb[2] + zb[3])));
-        bad |= nr[b] > 0 && !(Z >= kZLow && Z <= kZHigh);
-        const float f = nr[b] > 0 ? recip(Z) : 0.f;
+        for (int b = 0; b < 2; b++) {
+          nr[b] = visible(blk * 32 + 16 * b + r16);
+          products<T>(kf, blk & 1, b, x[b]);
+          float m = kNegInf;
 #pragma unroll
-        for (int k = 0; k < T; k++)
+          for (int k = 0; k < T; k++)
 #pragma unroll
-          for (int i = 0; i < 4; i++) acc[k][i] = fmaf(x[b][k][i], f, acc[k][i]);
+            for (int i = 0; i < 4; i++) m = fmaxf(m, sees(k, i, nr[b]) ? x[b][k][i] * c : kNegInf);
+          lds.z[1][16 * b + r16][4 * wave + gq] = m;
+        }
+        wait_vm<0>();
+        bar();
+#pragma unroll
+        for (int b = 0; b < 2; b++) {
+          float m = exchange<true>(1, 16 * b + r16);
+          m = m > kNegInf ? m : -kNegInf;
+          float4_t z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int k = 0; k < T; k++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+              const float v = rel_exp2(fmaf(x[b][k][i], c, -m));
+              x[b][k][i] = sees(k, i, nr[b]) ? v : 0.f;
+              z[i] += x[b][k][i];
+            }
+          lds.z[0][16 * b + r16][4 * wave + gq] = (z[0] + z[1]) + (z[2] + z[3]);
+        }
+        bar();
+        float f[2];
+#pragma unroll
+        for (int b = 0; b < 2; b++) {
+          const float Z = exchange<false>(0, 16 * b + r16);
+          f[b] = nr[b] > 0 && Z > 0.f ? recip(Z) : 0.f;
+        }
+        add(x, f);
+        if (blk % kFlush == kFlush - 1) flush<T>(acc);
       }
-      if (blk % kFlush == kFlush - 1) flush<T>(acc);
     }
     flush<T>(acc);
-    bar();  // every wave's reads are done
-    // The waves hold the same normalisers, so they agree.
-    if (__builtin_amdgcn_ballot_w64(bad) != 0) return false;
     put<T>(0, p.accumulate != 0);
-    return true;
   }
 
   // Two passes: `blocks` blocks of 32 rows of r's array from row0 through the
@@ -398,82 +478,117 @@ struct Window {
   }
 
   // Pass 1 over the keys, with the group's row tiles t0 + wave + kNW * k in
-  // the waves' registers: each row's normaliser. MODE 0: without a reference;
-  // 1: each row's maximum, into lds.g.m; 2: relative to it.
-  template <int T, int MODE>
+  // the waves' registers: each row's normaliser, without a reference, or (REF)
+  // relative to one that trails the lane's maximum by up to 2^kSlack, so that
+  // it hardly ever moves; the row's goes to lds.g.m.
+  template <int T, bool REF>
   __device__ __forceinline__ void normalisers(int row0, int t0) const {
+    constexpr float kSlack = 64.0f;
     const int gq = lane >> 4, r16 = lane & 15;
     u32x4 qf[T][KS];
     load_tiles<T>(qf, qr, row0 + 16 * t0, 0);
     auto at = [&](int k) { return (t0 + wave + kNW * k) * 16 + 4 * gq; };
-    float4_t z[T], m[MODE == 2 ? T : 1];
+    float4_t z[T], m[REF ? T : 1];
 #pragma unroll
     for (int k = 0; k < T; k++) {
-      z[k] = MODE == 1 ? float4_t{kNegInf, kNegInf, kNegInf, kNegInf} : float4_t{0.f, 0.f, 0.f, 0.f};
-      if (MODE == 2) m[k] = *reinterpret_cast<const float4_t *>(lds.g.m + at(k));
+      z[k] = float4_t{0.f, 0.f, 0.f, 0.f};
+      if (REF) m[k] = float4_t{kNegInf, kNegInf, kNegInf, kNegInf};
     }
-    auto fold = [&](int k, int i, float a, bool sees) {
-      float x = MODE == 2 ? fmaf(a, c, -m[MODE == 2 ? k : 0][i]) : a * c;
-      if (!sees) x = kNegInf;
-      if (MODE == 1) z[k][i] = fmaxf(z[k][i], x);
-      else z[k][i] += MODE == 2 ? rel_exp2(x) : fast_exp2(x);
+    auto fold = [&](const float4_t (&a)[T], auto sees) {
+      if constexpr (!REF) {
+#pragma unroll
+        for (int k = 0; k < T; k++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) z[k][i] += fast_exp2(sees(k, i) ? a[k][i] * c : kNegInf);
+      } else {
+        bool up = false;
+#pragma unroll
+        for (int k = 0; k < T; k++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) up |= sees(k, i) && a[k][i] * c > m[k][i] + kSlack;
+        if (__builtin_amdgcn_ballot_w64(up) != 0) {
+#pragma unroll
+          for (int k = 0; k < T; k++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+              const float x = a[k][i] * c;
+              if (sees(k, i) && x > m[k][i] + kSlack) {
+                z[k][i] = z[k][i] > 0.f ? z[k][i] * fast_exp2(m[k][i] - x) : 0.f;
+                m[k][i] = x;
+              }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < T; k++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) z[k][i] += rel_exp2(sees(k, i) ? fmaf(a[k][i], c, -m[k][i]) : kNegInf);
+      }
     };
     // Blocks of keys that every row sees, then the others with the mask.
     const int seen = n - p.nq + 1;
     const int plain = seen > 0 ? seen / 32 : 0, all = (n + 31) / 32;
-    if (plain > 0)
-      stream<T>(qf, kr, 0, plain, [&](int, const float4_t (&a)[T]) {
+    auto fold_all = [&](int, const float4_t (&a)[T]) { fold(a, [](int, int) { return true; }); };
+    int from = 0;
+    if (!REF && plain > kProbe) {
+      stream<T>(qf, kr, 0, kProbe, fold_all);
+      bool over = false;
 #pragma unroll
-        for (int k = 0; k < T; k++)
+      for (int k = 0; k < T; k++)
 #pragma unroll
-          for (int i = 0; i < 4; i++) fold(k, i, a[k][i], true);
-      });
+        for (int i = 0; i < 4; i++) over |= !(z[k][i] <= kZHigh);
+      if (over) lds.bad = 1;
+      bar();
+      if (lds.bad) return;  // every wave: it is written again after a barrier of the next blocks only
+      from = kProbe;
+    }
+    if (plain > from) stream<T>(qf, kr, from * 32, plain - from, fold_all);
     if (all > plain)
       stream<T>(qf, kr, plain * 32, all - plain, [&](int h, const float4_t (&a)[T]) {
         const int key = (plain * 2 + h) * 16 + r16;
-#pragma unroll
-        for (int k = 0; k < T; k++)
-#pragma unroll
-          for (int i = 0; i < 4; i++) fold(k, i, a[k][i], key < lds.g.nr[at(k) + i]);
+        fold(a, [&](int k, int i) { return key < lds.g.nr[at(k) + i]; });
       });
     bool bad = false;
 #pragma unroll
     for (int k = 0; k < T; k++) {
-      float4_t v;
+      float4_t f, M;
 #pragma unroll
       for (int i = 0; i < 4; i++) {
-        v[i] = reduce16<MODE == 1>(z[k][i]);
         const bool live = lds.g.nr[at(k) + i] > 0;
-        if (MODE == 0) bad |= live && !(v[i] >= kZLow && v[i] <= kZHigh);
-        if (MODE == 1) v[i] = live && v[i] > kNegInf ? v[i] : 0.f;
-        else v[i] = live && v[i] > 0.f ? recip(v[i]) : 0.f;
-        // Relative to this, every exp of a row that adds nothing is 0.
-        if (MODE == 2 && v[i] == 0.f) m[MODE == 2 ? k : 0][i] = -kNegInf;
+        float Z = z[k][i];
+        if (REF) {
+          const float ml = m[REF ? k : 0][i];
+          M[i] = reduce16<true>(ml);
+          Z = Z > 0.f ? Z * fast_exp2(ml - M[i]) : 0.f;
+        }
+        Z = reduce16<false>(Z);
+        if (!REF) bad |= live && !(Z >= kZLow && Z <= kZHigh);
+        f[i] = live && Z > 0.f ? recip(Z) : 0.f;
+        if (REF && f[i] == 0.f) M[i] = -kNegInf;
       }
       if (r16 == 0) {
-        *reinterpret_cast<float4_t *>((MODE == 1 ? lds.g.m : lds.g.f) + at(k)) = v;
-        if (MODE == 2) *reinterpret_cast<float4_t *>(lds.g.m + at(k)) = m[MODE == 2 ? k : 0];
+        *reinterpret_cast<float4_t *>(lds.g.f + at(k)) = f;
+        if (REF) *reinterpret_cast<float4_t *>(lds.g.m + at(k)) = M;
       }
     }
-    if (MODE == 0 && bad) lds.bad = 1;
+    if (bad) lds.bad = 1;
   }
 
-  template <int MODE>
+  template <bool REF>
   __device__ __forceinline__ void normalise(int row0, int tiles) const {
     const int slots = (tiles + kNW - 1) / kNW;  // per wave, at most kRowTiles
-    if (MODE == 0) {
-      if (slots <= 2) fresh().template normalisers<2, 0>(row0, 0);
-      else if (slots <= 4) fresh().template normalisers<4, 0>(row0, 0);
-      else fresh().template normalisers<kRowTiles, 0>(row0, 0);
-    } else {
-#pragma unroll 1
-      for (int k = 0; k < slots; k++) fresh().template normalisers<1, MODE>(row0, kNW * k);
+    if (slots <= 2) fresh().template normalisers<2, REF>(row0, 0);
+    else if (slots <= 4) fresh().template normalisers<4, REF>(row0, 0);
+    else if constexpr (!REF) fresh().template normalisers<kRowTiles, REF>(row0, 0);
+    else {
+      // References take registers: two passes over the keys.
+      fresh().template normalisers<4, REF>(row0, 0);
+      fresh().template normalisers<kRowTiles - 4, REF>(row0, 4 * kNW);
     }
     bar();
   }
 
   // Pass 2, over the group's rows with tiles k0 .. k0 + T - 1 of the keys in
-  // the waves' registers: their column sums. REF: relative to the rows' maxima.
+  // the waves' registers: their column sums. REF: relative to the rows' references.
   template <int T, bool MASK, bool REF>
   __device__ __forceinline__ void columns(int row0, int blocks, int k0) const {
     const int gq = lane >> 4, r16 = lane & 15;
@@ -526,10 +641,9 @@ struct Window {
         lds.g.f[at] = lds.g.m[at] = 0.f;
       }
       bar();
-      normalise<0>(row0, 2 * blocks);
+      normalise<false>(row0, 2 * blocks);
       if (lds.bad) {
-        normalise<1>(row0, 2 * blocks);
-        normalise<2>(row0, 2 * blocks);
+        normalise<true>(row0, 2 * blocks);
         columns_of<true>(row0, blocks, slots, seen);
       } else {
         columns_of<false>(row0, blocks, slots, seen);
@@ -556,15 +670,15 @@ __global__ __launch_bounds__(kNW * 64) __attribute__((amdgpu_waves_per_eu(2))) v
                     __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), (int)(threadIdx.x % kWave),
                     p.scale * kLog2e, p.scores + (size_t)unit * p.cap};
   const int slots = ((n + 15) / 16 + kNW - 1) / kNW;  // 16-key tiles per wave
-  bool done = false;
-  if (slots <= 2) done = w.fresh().template one_pass<2, 2>();
-  else if (slots <= 4) done = w.fresh().template one_pass<4, 4>();
+  if (slots <= 2) w.fresh().template one_pass<2, 2>();
+  else if (slots <= 4) w.fresh().template one_pass<4, 4>();
   else if (slots <= kKeyTiles) {
     // The causal mask reaches the last two tiles of a wave only, or all.
-    if (n >= p.nq && (n - p.nq + 1) / (16 * kNW) >= kKeyTiles - 2) done = w.fresh().template one_pass<6, 2>();
-    else done = w.fresh().template one_pass<6, 6>();
+    if (n >= p.nq && (n - p.nq + 1) / (16 * kNW) >= kKeyTiles - 2) w.fresh().template one_pass<6, 2>();
+    else w.fresh().template one_pass<6, 6>();
+  } else {
+    w.two_pass(slots);
   }
-  if (!done) w.two_pass(slots);
 }
 
 }  // namespace

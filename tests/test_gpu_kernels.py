@@ -580,6 +580,37 @@ def test_accumulate_scores_nan_and_inf(D, G, nq, n, where, value):
     assert (got[n:] == 0.25).all()
 
 
+@pytest.mark.parametrize("n", [700, 2000])
+def test_accumulate_scores_time_by_logit_size(n):
+    """Larger logits cost little: every row of these heads is outside what
+    float32 exps take without a reference at 64 times unit queries, and well
+    inside at 6 times. One pass over the keys (n = 700) measured 1.0 and 1.35
+    times the time at unit queries, two (n = 2000) 1.0 and 1.9; an online
+    maximum for every row, whatever its size, 2.2 and 1.9."""
+    k = kvr()
+    S, L, Hkv, G, D, nq = 4, 32, 4, 7, 128, 128
+    g = torch.Generator(device=DEV).manual_seed(n)
+    K = torch.randn((S, L, Hkv, n, D), generator=g, device=DEV).to(torch.bfloat16)
+    q = torch.randn((S, L, Hkv * G, nq, D), generator=g, device=DEV).to(torch.bfloat16)
+    cache, lens = k.Cache(K, K, None), torch.full((S,), n, dtype=torch.int32, device=DEV)
+    sc = torch.zeros((S, L, Hkv, n), device=DEV)
+
+    def us(mul):
+        qm, ts = q * mul, []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            k.accumulate_scores(cache, lens, qm, 1.0 / math.sqrt(D), sc)
+            b.record()
+            torch.cuda.synchronize()
+            ts.append(a.elapsed_time(b) * 1e3)
+        return min(ts)
+
+    t = [us(1.0), us(6.0), us(64.0)]
+    say("window scores, us at 1, 6 and 64 times unit queries:", *("%.0f" % x for x in t))
+    assert t[1] <= 1.5 * t[0] and t[2] <= 2.2 * t[0]
+
+
 # ------------------------------------------------------------ entropy
 
 ENT_CASES = [
