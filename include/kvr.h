@@ -192,9 +192,9 @@ size_t kvr_decode_attn_workspace_size(const kvr_cache *cache, const kvr_prefix *
  * bfloat16: a NaN logit counts as no probability, and a row with a logit of
  * +inf, or without a finite one, adds nothing to any slot.
  * Results are bitwise reproducible (the bf16 kernel adds its float32 sums of
- * at most 16 rows in float64, in a fixed order). Errors: as kvr_decode_attn,
- * and KVR_EUNSUPPORTED when cap exceeds 8192 slots (bf16) or (D + 2 cap) floats
- * exceed 64 KiB (float32).
+ * at most 32 rows in float64, in a fixed order). Errors: as kvr_decode_attn,
+ * and KVR_EUNSUPPORTED when cap exceeds 8192 slots (bf16: a float64 sum per
+ * slot in 64 KiB of LDS) or (D + 2 cap) floats exceed 64 KiB (float32).
  */
 int kvr_accumulate_scores(const kvr_cache *cache, const int32_t *len, const void *q_win,
                           int32_t nq, int32_t Hq, float scale, float *scores,

@@ -32,10 +32,11 @@
 //     with an online maximum throughout take 1.04-1.16 and 6.3-6.8. There a NaN
 //     logit counts as no probability, and a row with an infinite logit (or
 //     none finite) adds nothing, so neither reaches another key's or row's score.
-// Column sums are float32 over at most 8 rows a lane, then float64 in a
-// fixed order, so the scores are bitwise reproducible and as exact as their
-// float32 result (commit shape 2.7e-8 in the 2-norm against float64; 2.9e-8, but
-// 1-2% less time, with 16 rows).
+// Column sums are float32 over at most 32 rows (8 a lane, then a quad of
+// lanes), then float64 in a fixed order over all of a head's rows, so the
+// scores are bitwise reproducible and as exact as their float32 result (commit
+// shape 2.7e-8 in the 2-norm against float64; 2.9e-8, but 1-2% less time, with
+// 64 rows).
 // Measured and not kept: products interleaved one by one with the exps, 32x32
 // products, two or three independent workgroups per CU, four waves per SIMD
 // (all 3.4 to 4.0 ms on 4096 keys, the clock falling from 2.1 to 1.6 GHz as
@@ -302,16 +303,23 @@ struct Window {
     }
   }
 
-  // The quads' sums, written by the first; `add`: to the stored scores.
+  // The quads' sums, written by the first quad's lanes. With several groups of
+  // window rows (two passes) a key's sum is carried in float64 from the first
+  // group (`begin`) to the last (`end`), by the same lane in each.
   template <int T>
-  __device__ __forceinline__ void put(int k0, bool add) const {
+  __device__ __forceinline__ void put(int k0, bool begin, bool end) const {
+    extern __shared__ double carried[];  // [cap], with several groups only
 #pragma unroll
     for (int k = 0; k < T; k++) {
       double v = lds.sum[k][threadIdx.x];
       v += shfl_xor(v, 4);
       v += shfl_xor(v, 8);
       const int j = (wave + kNW * (k0 + k)) * 16 + 4 * (lane >> 4) + (lane & 15);
-      if ((lane & 15) < 4 && j < n) sc[j] = add ? sc[j] + (float)v : (float)v;
+      if ((lane & 15) < 4 && j < n) {
+        if (!begin) v += carried[j];
+        if (!end) carried[j] = v;
+        else sc[j] = p.accumulate ? sc[j] + (float)v : (float)v;
+      }
     }
   }
 
@@ -453,7 +461,7 @@ struct Window {
       }
     }
     flush<T>(acc);
-    put<T>(0, p.accumulate != 0);
+    put<T>(0, true, true);
   }
 
   // Two passes: `blocks` blocks of 32 rows of r's array from row0 through the
@@ -590,7 +598,7 @@ struct Window {
   // Pass 2, over the group's rows with tiles k0 .. k0 + T - 1 of the keys in
   // the waves' registers: their column sums. REF: relative to the rows' references.
   template <int T, bool MASK, bool REF>
-  __device__ __forceinline__ void columns(int row0, int blocks, int k0) const {
+  __device__ __forceinline__ void columns(int row0, int blocks, int k0, bool last) const {
     const int gq = lane >> 4, r16 = lane & 15;
     u32x4 kf[T][KS];
     load_tiles<T>(kf, kr, 0, k0);
@@ -610,20 +618,20 @@ struct Window {
       if (h % (2 * kFlush) == 2 * kFlush - 1) flush<T>(acc);
     });
     flush<T>(acc);
-    put<T>(k0, p.accumulate != 0 || row0 > 0);
+    put<T>(k0, row0 == 0, last);
   }
 
   template <bool REF>
-  __device__ __forceinline__ void columns_of(int row0, int blocks, int slots, int seen) const {
+  __device__ __forceinline__ void columns_of(int row0, int blocks, int slots, int seen, bool last) const {
 #pragma unroll 1
     for (int k0 = 0; k0 < slots; k0 += kKeyTiles) {
       const int kt = slots - k0;
       // Uniform over the workgroup (every wave meets the barriers inside).
       const bool mask = kNW * (k0 + kKeyTiles) * 16 > seen;
-      if (kt <= 2) fresh().template columns<2, true, REF>(row0, blocks, k0);
-      else if (kt <= 4) fresh().template columns<4, true, REF>(row0, blocks, k0);
-      else if (mask) fresh().template columns<kKeyTiles, true, REF>(row0, blocks, k0);
-      else fresh().template columns<kKeyTiles, false, REF>(row0, blocks, k0);
+      if (kt <= 2) fresh().template columns<2, true, REF>(row0, blocks, k0, last);
+      else if (kt <= 4) fresh().template columns<4, true, REF>(row0, blocks, k0, last);
+      else if (mask) fresh().template columns<kKeyTiles, true, REF>(row0, blocks, k0, last);
+      else fresh().template columns<kKeyTiles, false, REF>(row0, blocks, k0, last);
     }
   }
 
@@ -644,9 +652,9 @@ struct Window {
       normalise<false>(row0, 2 * blocks);
       if (lds.bad) {
         normalise<true>(row0, 2 * blocks);
-        columns_of<true>(row0, blocks, slots, seen);
+        columns_of<true>(row0, blocks, slots, seen, row0 + rows == R);
       } else {
-        columns_of<false>(row0, blocks, slots, seen);
+        columns_of<false>(row0, blocks, slots, seen, row0 + rows == R);
       }
     }
   }
@@ -689,8 +697,12 @@ hipError_t launch_accumulate_scores(const ScoreParams &p, hipStream_t stream) {
     const size_t lds = ((size_t)p.D + 2 * (size_t)p.cap) * sizeof(float);
     hipLaunchKernelGGL(window_scores_kernel<float>, grid, dim3(64), lds, stream, p);
   } else {
-    if (p.D == 128) hipLaunchKernelGGL(window_scores_bf16<128>, grid, dim3(kNW * kWave), 0, stream, p);
-    else hipLaunchKernelGGL(window_scores_bf16<64>, grid, dim3(kNW * kWave), 0, stream, p);
+    // Sums carried between groups of window rows (two passes): 64 KiB at the
+    // longest cache, 8192 slots, beside 51 KiB of the kernel's own, of the
+    // 160 KiB of a CU, whose registers hold one workgroup.
+    const size_t lds = p.G * p.nq > kRG && p.cap > kNW * kKeyTiles * 16 ? (size_t)p.cap * sizeof(double) : 0;
+    if (p.D == 128) hipLaunchKernelGGL(window_scores_bf16<128>, grid, dim3(kNW * kWave), lds, stream, p);
+    else hipLaunchKernelGGL(window_scores_bf16<64>, grid, dim3(kNW * kWave), lds, stream, p);
   }
   return hipGetLastError();
 }

@@ -237,7 +237,7 @@ def test_lds_limits_rejected_on_host():
     c = _cache(kvr, cap=16129)
     pol = kvr.c_policy(256, 32, 15872)
     assert kvr.lib.kvr_evict_topb(ctypes.byref(c), 16, None, 16, ctypes.byref(pol), None, None) == -2
-    # Window recompute (bf16): one 64-bit fixed-point accumulator per slot.
+    # Window recompute (bf16): one float64 sum per slot, carried between groups of window rows.
     c = _cache(kvr, cap=8193)
     assert kvr.lib.kvr_accumulate_scores(ctypes.byref(c), 16, 16, 8, 8, 1.0, 16, 0, None) == -2
     c = _cache(kvr, cap=8192, k=0, v=0)  # within the limit: fails later, on the NULL cache pointers

@@ -580,6 +580,40 @@ def test_accumulate_scores_nan_and_inf(D, G, nq, n, where, value):
     assert (got[n:] == 0.25).all()
 
 
+@pytest.mark.parametrize("D,G,nq,n,std", [(64, 16, 1400, 1500, 1.0), (128, 8, 700, 1000, 1.0), (64, 16, 1400, 1500, 40.0),
+                                          (64, 15, 600, 8192, 1.0)])
+def test_accumulate_scores_many_rows(D, G, nq, n, std):
+    """Windows of many groups of rows keep their sums in float64 between the
+    groups: at unit scale the error in the 2-norm is that of one rounding to
+    float32 (2^-24 / sqrt(12) / 0.69 = 2.5e-8 over values spread evenly between
+    powers of two; the exps' own errors average out), here at most 1.4 times
+    that, where a float32 sum per group gave 3 times. Wide logits (std 40, their
+    error that of the products, 2^-24 of logits of about 200) take the
+    references' route; 8192 slots need the largest LDS."""
+    k = kvr()
+    g = torch.Generator().manual_seed(n)
+    K, q = randn((1, 1, 1, n, D), g, torch.bfloat16), randn((1, 1, G, nq, D), g, torch.bfloat16, std)
+    scale = 1.0 / math.sqrt(D)
+    sc = torch.zeros((1, 1, 1, n), device=DEV)
+    say("window scores of many rows", D, G, nq, n, std)
+    Kd = K.to(DEV)
+    for acc in (False, True):
+        k.accumulate_scores(k.Cache(Kd, Kd, None), torch.tensor([n], dtype=torch.int32, device=DEV), q.to(DEV), scale, sc,
+                            accumulate=acc)
+        torch.cuda.synchronize()
+        if not acc:
+            got = sc[0, 0, 0].cpu().double()
+    late = torch.arange(n)[None, :] >= n - (nq - 1 - torch.arange(nq))[:, None]
+    ref = torch.zeros(n, dtype=torch.float64)
+    for h in range(G):
+        x = torch.matmul(q[0, 0, h].double(), K[0, 0, 0].double().T) * scale
+        ref += torch.softmax(x.masked_fill(late, -math.inf), -1).sum(0)
+    err = ((got - ref).norm() / ref.norm()).item()
+    say("  error", err)
+    assert err <= (3.5e-8 if std == 1.0 else 2e-5)
+    assert torch.equal(sc[0, 0, 0].cpu(), (2.0 * got).float())
+
+
 @pytest.mark.parametrize("n", [700, 2000])
 def test_accumulate_scores_time_by_logit_size(n):
     """Larger logits cost little: every row of these heads is outside what
