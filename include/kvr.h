@@ -171,7 +171,12 @@ int kvr_decode_attn(const kvr_cache *cache, const kvr_prefix *prefix, const int3
                     const kvr_policy *policy, float *scores, void *workspace,
                     size_t workspace_bytes, hipStream_t stream);
 
-/* Workspace bytes kvr_decode_attn needs for this geometry (0 without prefix). */
+/*
+ * Workspace bytes kvr_decode_attn needs for this geometry (0 without prefix).
+ * They are also enough for calls with the same L, Hq, Hkv and D and fewer
+ * prefixes, fewer candidates per prefix or shorter prefixes, so a program that
+ * asks once for its largest batch and longest context keeps one buffer.
+ */
 size_t kvr_decode_attn_workspace_size(const kvr_cache *cache, const kvr_prefix *prefix,
                                       int32_t Hq);
 

@@ -81,11 +81,9 @@ const char *kvr_last_error(void) { return g_err; }
 size_t kvr_decode_attn_workspace_size(const kvr_cache *cache, const kvr_prefix *prefix, int32_t Hq) {
   if (!cache || !prefix || prefix->P <= 0 || cache->dtype != KVR_BF16) return 0;
   if (cache->Hkv <= 0 || Hq <= 0 || Hq % cache->Hkv != 0 || cache->S % prefix->P != 0) return 0;
-  int ns = 1, span = 1, nw = 1, pitch = 1;
-  const int rows = (cache->S / prefix->P) * (Hq / cache->Hkv);
-  kvr::plan_prefix_splits(cache->D, cache->S, prefix->P, cache->L, cache->Hkv, prefix->plen, rows, 0, &ns, &span, &nw,
-                          &pitch);
-  return kvr::attn_workspace_bytes(cache->S, cache->L, Hq, cache->D, ns);
+  const long records = kvr::prefix_records_bound(cache->D, cache->S, prefix->P, cache->L, cache->Hkv, prefix->plen,
+                                                 Hq / cache->Hkv);
+  return kvr::attn_workspace_bytes(cache->S, cache->L, Hq, cache->D, (int)((records + cache->S - 1) / cache->S));
 }
 
 }  // extern "C"

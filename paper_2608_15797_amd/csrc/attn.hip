@@ -1741,6 +1741,39 @@ void plan_prefix_splits(int D, int S, int P, int L, int Hkv, int plen, int rows,
   *nwaves = (int)((heads * *pitch + sp - 1) / sp);
 }
 
+// Over the plans of P' <= P prefixes of plen' <= plen keys with C' <= S / P
+// candidates each, the most partial records that one takes per query head. A
+// plan has at most ceil(plen' / least) + 1 of them per sequence and, its spans
+// no shorter than the slots' share, ceil(slots / units) + 1. The least span is
+// not monotone in the number of suffixes, so the largest P' below its line
+// counts too, and the longest prefix of each of its steps.
+long prefix_records_bound(int D, int S, int P, int L, int Hkv, int plen, int G) {
+  const long heads = (long)L * Hkv;
+  auto pieces = [&](long units) {
+    long most = 0;
+    for (int n : {plen < 2048 ? plen : 2048, plen < 8192 ? plen : 8192, plen}) {
+      const long least = least_span(n, units), k = (n + least - 1) / least;
+      most = k > most ? k : most;
+    }
+    return most;
+  };
+  const int most = 64 / G > 1 ? 64 / G : 1;  // candidates per prefix that a call takes
+  const int C = S / P < most ? S / P : most;
+  long records = 0;
+  for (int c = 1; c <= C; c++) {
+    const long slots = slots_for(D, (c * G + 15) / 16, false);
+    auto bound = [&](long pp) {
+      const long by_keys = c * pp * pieces(c * pp * heads), by_slots = c * (slots / heads + 1) + c * pp;
+      const long r = c * pp + (by_keys < by_slots ? by_keys : by_slots);
+      records = r > records ? r : records;
+    };
+    bound(P);
+    const long few = kSplitSuffixUnits / (heads * c);
+    if (few >= 1 && few < P) bound(few);
+  }
+  return records;
+}
+
 bool rows_with_suffix(const AttnParams &p, const EntropyBatch &e) {
   return (long)p.S * p.L * p.Hkv <= kSplitSuffixUnits &&
          rows_outlast(e, (double)p.P * p.L * p.Hkv * p.plen * (4 * p.D), 1.0);

@@ -41,12 +41,15 @@ struct AttnParams {
 };
 
 // Work plan of the prefix path (rows = C * G query rows per prefix unit;
-// ent_rows = logit rows computed in the context launch, 0 for none);
-// identical on the size query and the call. The plan with ent_rows > 0 never
-// has more splits than the one without.
+// ent_rows = logit rows computed in the context launch, 0 for none). The plan
+// with ent_rows > 0 never has more splits than the one without.
 void plan_prefix_splits(int D, int S, int P, int L, int Hkv, int plen, int rows, int ent_rows, int *nsplit,
                         int *span, int *nwaves, int *pitch);
 size_t attn_workspace_bytes(int S, int L, int Hq, int D, int nsplit);
+// Partial records per query head (sequences * splits) that cover the plan of
+// this geometry and of every one with fewer prefixes, fewer candidates per
+// prefix or shorter prefixes: the size query's.
+long prefix_records_bound(int D, int S, int P, int L, int Hkv, int plen, int G);
 
 struct EntropyBatch;
 // Whether the logit rows of a bf16 prefix call go with the suffix launch (four

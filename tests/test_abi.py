@@ -174,6 +174,35 @@ def test_prefix_workspace_size_matches_split_plan():
     assert n % rec == 0 and n // rec >= 2
 
 
+def test_prefix_workspace_covers_smaller_geometries():
+    """The size asked for the largest geometry is enough for every call with
+    fewer prefixes, fewer candidates per prefix or a shorter prefix (what a call
+    needs is in its refusal), across the steps of the plan's least span."""
+    import random
+    from paper_2608_15797_amd import kvr
+
+    def size(P, C, L, plen, Hkv, G):
+        c, p = _cache(kvr, S=P * C, L=L, Hkv=Hkv, cap=512), kvr.c_prefix(16, 16, P, plen)
+        return kvr.lib.kvr_decode_attn_workspace_size(ctypes.byref(c), ctypes.byref(p), Hkv * G)
+
+    def need(P, C, L, plen, Hkv, G):
+        c, p = _cache(kvr, S=P * C, L=L, Hkv=Hkv, cap=512), kvr.c_prefix(16, 16, P, plen)
+        assert kvr.lib.kvr_decode_attn(ctypes.byref(c), ctypes.byref(p), 16, 16, Hkv * G, 1.0, None, None, None, 16,
+                                       None, None, None, 0, None) == -4
+        return int(kvr.lib.kvr_last_error().decode().split("workspace of ")[1].split()[0])
+
+    pairs = [((1, 1, 28, 8193), (1, 1, 28, 8192)), ((37, 1, 28, 8192), (36, 1, 28, 8192)),
+             ((8, 1, 28, 2049), (8, 1, 28, 2048)), ((16, 8, 28, 8192), (4, 8, 28, 8192)),
+             ((16, 5, 3, 20000), (16, 1, 3, 2047))]
+    rng = random.Random(3)
+    for _ in range(400):
+        big = (rng.randint(1, 64), rng.randint(1, 10), rng.randint(1, 40), int(2 ** rng.uniform(4, 15)))
+        pairs.append((big, (rng.randint(1, big[0]), rng.randint(1, big[1]), big[2], rng.randint(1, big[3]))))
+    for big, small in pairs:
+        assert size(*big, 2, 6) >= need(*big, 2, 6), big
+        assert size(*big, 2, 6) >= need(*small, 2, 6), (big, small)
+
+
 def test_fork_rejects_bad_arguments_on_host():
     from paper_2608_15797_amd import kvr
     src = _cache(kvr)
