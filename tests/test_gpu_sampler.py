@@ -171,13 +171,17 @@ def test_sampler_rejects_bad_settings():
     (327680, 64, torch.bfloat16), (327688, 64, torch.bfloat16),  # 16 splits of one round, and one vector more
 ])
 def test_sampler_routes_agree(kind, V, top_k, dt):
-    """Rows that start 16-byte aligned (a split in registers at once, or
-    streamed where the splits are longer) and the same rows at a byte offset
-    that they do not (scalar loads) give the same k best logits, so the same
-    tokens; the entropies differ by the order of their float32 sums (1e-5 of a
-    value of at most ln V = 12.7). Rows of equal logits, of rising ones and of
-    a few lanes that hold all the large ones have more candidates than the
-    register route ranks at once; "ninf" rows have fewer finite logits than k."""
+    """Rows that start 16-byte aligned and the same rows off that alignment give
+    the oracle's tokens and the same k best logits. Splits of at most 2560
+    vectors are held in registers at once, at either alignment (the vectors
+    start at the row's first aligned logit); the 327688 logits with top_k 64
+    stream instead, in vectors where aligned and one by one where not. The
+    entropies differ by the order of their float32 sums (1e-5 of a value of at
+    most ln V = 12.7). Rows of equal logits, of rising ones (whole runs of
+    equal ones in bfloat16) and of a few lanes that hold all the large ones
+    have more candidates than the register route ranks at once; "ninf" rows
+    have fewer finite logits than k. The oracle sorts every row once, so long
+    rows are compared with it at one of the steps only."""
     k = kvr()
     say("sampler routes", kind, V, top_k, dt)
     R = 3
@@ -208,5 +212,6 @@ def test_sampler_routes_agree(kind, V, top_k, dt):
         H2, tok2 = _run(off, V, smp)
         assert np.array_equal(tok, tok2)
         assert np.abs(H - H2).max() <= 1e-5 * 12.7
-        if kind in ("normal", "negative", "clustered"):
-            _check_tokens(host(x), V, smp, tok)
+        if step == 77 or V < 50000:
+            exact, loose = _check_tokens(host(x), V, smp, tok)
+            say(" ", step, "tokens equal to the oracle's:", exact, "within rounding:", loose)
