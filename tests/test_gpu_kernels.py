@@ -264,17 +264,23 @@ def test_decode_attn_f32_large_values(D, G, n):
     (2, 1, 1, 2, 6, 128, 4001, 512, torch.bfloat16),
     (3, 3, 1, 1, 16, 64, 16384, 100, torch.bfloat16),
     (64, 8, 10, 4, 4, 64, 700, 30, torch.bfloat16),
+    # Ragged suffixes of 2048 units (the last with four waves each) and of 2112 (one wave each, at D = 128), one and
+    # six context records per row.
+    (32, 32, 32, 2, 6, 128, 70, 40, torch.bfloat16),
+    (33, 11, 32, 2, 6, 128, 70, 40, torch.bfloat16),
+    (33, 3, 32, 2, 2, 128, 2600, 50, torch.bfloat16),
 ], ids=lambda c: "S%dP%dL%dHkv%dD%d_plen%d" % (*c[:4], *c[5:7]))
 def test_decode_attn_prefix_plans(case):
     test_decode_attn_prefix(case)
 
 
-# Few units: four waves per unit. Live lengths end in every wave's share (chunks of 16 keys), logits in and out of the
-# window, groups of 1 and 16 heads, caches whose stored scores exceed the prefetched ones.
+# Launches of 4 to 672 units: logits in and out of the window, groups of 1 and 16 heads, caches whose stored scores
+# exceed the prefetched ones, and at D = 128 lengths over several chunks in more units than the chip has CUs.
 @pytest.mark.parametrize("case", [
     (4, 1, 1, 16, 128, 30, 8, 40, torch.bfloat16), (6, 1, 2, 1, 64, 17, 5, 60, torch.bfloat16),
     (2, 2, 2, 7, 128, 300, 64, 300, torch.bfloat16), (8, 4, 16, 4, 64, 40, 8, 30, torch.bfloat16),
-    (9, 4, 16, 4, 64, 40, 8, 30, torch.bfloat16),
+    (9, 4, 16, 4, 64, 40, 8, 30, torch.bfloat16), (7, 10, 8, 3, 128, 90, 16, 70, torch.bfloat16),
+    (6, 14, 8, 8, 128, 200, 32, 340, torch.bfloat16), (3, 2, 2, 2, 128, 500, 64, 400, torch.bfloat16),
 ], ids=lambda c: "S%dL%dHkv%dG%dD%d_B%d" % c[:6])
 def test_decode_attn_few_units(case):
     test_decode_attn_base_with_scores(case)
@@ -457,9 +463,9 @@ def test_evict_topb_ties_and_gpu_scores_selection(B, W, buffer, levels):
     (torch.bfloat16, 128, 16, 33, 130),    # 33 row blocks: the last pair is half empty
     (torch.bfloat16, 128, 1, 3, 40),       # fewer rows than one block
     (torch.bfloat16, 128, 7, 128, 300),    # a committed step's window on the 7B head shape
-    (torch.bfloat16, 128, 4, 8, 6144),     # largest cache of the LDS-ring kernel: 64-bit accumulator + ring = 64 KB
-    (torch.bfloat16, 64, 4, 8, 7500),      # beyond it at D = 64: the single-wave-stream kernel
-    (torch.bfloat16, 128, 4, 8, 8192),     # largest cache: the accumulator alone fills 64 KB of LDS
+    (torch.bfloat16, 128, 4, 8, 6144),     # long caches: two passes over the keys, many groups of key tiles
+    (torch.bfloat16, 64, 4, 8, 7500),
+    (torch.bfloat16, 128, 4, 8, 8192),     # largest cache
 ])
 def test_accumulate_scores(dt, D, G, nq, cap):
     """kvr_accumulate_scores equals the oracle's causal window re-computation,
@@ -489,8 +495,8 @@ def test_accumulate_scores(dt, D, G, nq, cap):
     got = sc.cpu().double().numpy()
     for s, n in enumerate(lens):
         assert np.abs(got[s, ..., :n] - 2 * ref[s, ..., :n]).max() <= 2e-4
-    # Bitwise reproducible: the same call again gives the same bits (the
-    # column sums of the workgroup's waves are added in fixed point).
+    # Bitwise reproducible: the same call again gives the same bits (a key's
+    # column sums belong to one wave, which adds them in a fixed order).
     for _ in range(3):
         again = torch.full((S, L, Hkv, cap), 0.25, device=DEV)
         k.accumulate_scores(cache, lent, qw.to(DEV), scale, again, accumulate=False)
