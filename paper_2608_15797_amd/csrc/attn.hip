@@ -1276,9 +1276,8 @@ __global__ __launch_bounds__(64) void attn_prefix_rows_bf16(AttnParams p, Entrop
 //     lanes, and added to the G heads' sums in registers (GM >= G of them);
 //     the groups' sums meet in LDS.
 // One wave per unit with a key per lane (whole rows strided over the lanes,
-// read again for every head) took 1640 us for 8 x 28 x 4 units of 129-257
-// tokens (G = 7, D = 128); this takes 46 us
-// (184 MB, 4.0 TB/s).
+// read again for every head) took 1802 us for 8 x 28 x 4 units of 129-257
+// tokens (G = 7, D = 128); this takes 44 us (184 MB, 4.2 TB/s).
 // LDS: q rows [G][D], logits [G][ld]; the groups' sums [4][G][D] over both
 // once they are used.
 constexpr int kF32Threads = 256;
@@ -1485,8 +1484,8 @@ constexpr long kSplitSuffixUnits = 2048;
 constexpr double kRowBytes = 1900, kSampleRowBytes = 3800;
 // One-wave rows of an evicted-cache launch are worth a launch of their own,
 // four waves per row, where its units take less than this share of a row
-// (their bytes at full caches): 64 rows with 1024 units (143 MB) 57 us in the
-// launch and 38 apart, with 1536 (214 MB) 59 and 46; sampled, with 1024 units
+// (their bytes at full caches): 64 rows with 256 units 51 us in the launch and 29
+// apart, with 1024 (143 MB) 57 and 38, with 1536 (214 MB) 59 and 46; sampled, with 1024 units
 // 102 and 51, with 2048 104 and 66. With 7168 units sampled rows cost 5 us in
 // the launch.
 constexpr double kOwnShare = 0.8;
@@ -1525,7 +1524,8 @@ void launch_rows(const EntropyBatch &e, hipStream_t stream) {
   }
 }
 
-// The suffix kernel of few units, rows as in launch_own.
+// The suffix kernel of few units, with the logit rows of `e` (nullptr: none),
+// four waves each, in front of its units.
 template <int D>
 void launch_suffix_split(const AttnParams &p, const EntropyBatch *e, hipStream_t stream) {
   const int rows = e ? e->row0[e->nsets] : 0;

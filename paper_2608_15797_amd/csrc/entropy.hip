@@ -553,7 +553,8 @@ hipError_t launch_logit_entropy(const EntropyParams &p, hipStream_t stream) {
   b.row0[1] = p.R;
   b.nsets = 1;
   if (p.top_k <= 0) return launch_logit_entropy_batch(b, stream);
-  // Splits of one round; longer ones stream (entropy_kernel).
+  // Splits of one round; longer ones stream (entropy_kernel): rows beyond 327,680
+  // logits with top_k 64, beyond a million with top_k 20.
   const int nvec = p.V / 8;
   hipError_t e;
   if ((nvec + p.splits - 1) / p.splits <= kRoundVecs) {

@@ -254,7 +254,7 @@ __device__ __forceinline__ void entropy_row_wave(const EntropyParams &p, int row
 }
 
 // The same by a workgroup of NW waves (one wave's row is a chain of its
-// banks, about 25 us for 152064 logits, which a launch of few attention units
+// banks, about 50 us for 152064 logits, which a launch of few attention units
 // would wait for): a share of the vectors each, the triples merged by the
 // first. part: NW triples of LDS.
 template <typename T, int U, int NW>

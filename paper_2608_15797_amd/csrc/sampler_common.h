@@ -360,8 +360,8 @@ __device__ __forceinline__ void entropy_sample_row_wave(const EntropyParams &p, 
   // The buffer cut to the k best once it outgrows the wave: with the threshold
   // at the k-th best of what has streamed, candidates get rare (k per bank, then
   // k/2, k/3 ...) and most vectors are passed over by one vote: 102 us for
-  // 152064 logits beside few attention units, against 135 at the first bank's
-  // threshold until the buffer is full (57 for the entropy alone).
+  // 152064 logits beside few attention units, against 131 at the first bank's
+  // threshold until the buffer is full (50 for the entropy alone).
   auto tighten = [&]() {
     if (cs.cnt > kWave && cs.cnt > p.top_k) cand_reduce_any(cs, p.top_k, p.top_k, lane);
   };

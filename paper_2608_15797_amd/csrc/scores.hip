@@ -8,19 +8,17 @@
 //
 // bf16 caches: the R = G * nq window rows of one (sequence, layer, KV head)
 // form a dense [R x D] x [D x n] contraction, done on MFMA 16x16x32 bf16, one
-// workgroup of eight waves per head. What bounds it is the exps and the
-// products, which the matrix core and the vector unit do not overlap for this
-// shape (a 16x16x32 product keeps the vector unit from issuing for most of its
-// 16 cycles) and which run at the chip's power limit; so each exp and each
-// vector instruction counts:
+// workgroup of eight waves per head. What bounds it is vector issue and the
+// products, which overlap little (77% and 37% of the cycles over 42 commit and 6
+// prompt calls); so each exp and each vector instruction counts:
 //   - Heads of up to 768 keys (8 waves x 6 tiles of 16 keys in registers) take
 //     one pass: every product and every exp is formed once, and the waves
 //     exchange their rows' partial normalisers through LDS. On the commit
-//     shape (16 x 28 x 4 heads, 896 rows, 641-768 keys) 0.48 ms, against 1.03
+//     shape (16 x 28 x 4 heads, 896 rows, 641-768 keys) 0.44 ms, against 1.03
 //     for two passes over keys streamed through LDS.
 //   - Longer heads take two passes, the first with the window rows in
 //     registers and the keys streaming (normalisers), the second with the keys
-//     in registers and the rows streaming (column sums): 3.5 ms against 6.2
+//     in registers and the rows streaming (column sums): 3.5 ms against 6.4
 //     on 4096 keys.
 //   - No running maximum: a row's exps need no reference as long as its
 //     normaliser stays within 2^-80 .. 2^100, which is tested once per row. In
@@ -39,8 +37,7 @@
 // 64 rows).
 // Measured and not kept: products interleaved one by one with the exps, 32x32
 // products, two or three independent workgroups per CU, four waves per SIMD
-// (all 3.4 to 4.0 ms on 4096 keys, the clock falling from 2.1 to 1.6 GHz as
-// the cycles do).
+// (all 3.4 to 4.0 ms on 4096 keys).
 //
 // float32 caches take a plain one-wave-per-head kernel (one key per lane).
 #include <hip/hip_runtime.h>
