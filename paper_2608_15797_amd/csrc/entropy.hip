@@ -404,27 +404,55 @@ constexpr int kMergeThreads = 1024;
 // uniform. The first wave then has the softmax, the nucleus and the token. One wave
 // doing all of it in turn (a bit-by-bit threshold, then the sort) took 9.5 us
 // for 128 rows of 8 splits x 20 keys, this 4.7.
+// The comparisons grow with the square of the keys (1024 of them 30 us). More
+// than 256 are first cut to those that reach the leading bits of the top_k-th
+// largest of 256 groups' maxima, about top_k of them; all are ranked where more
+// than 256 do (many equal logits).
 __global__ __launch_bounds__(kMergeThreads) void sample_merge(EntropyParams p) {
-  __shared__ __align__(16) uint64_t keys[kMergeEntries];
+  constexpr int PARTS = 4, PT = kMergeThreads / PARTS;
+  __shared__ __align__(16) uint64_t all[kMergeEntries + PT];  // the splits' keys, then those that may win
   __shared__ int rank[kMergeEntries];
   __shared__ uint64_t sorted[kTopKMax];
+  __shared__ uint32_t group_max[PT];
+  __shared__ int count;
   __shared__ float uniform;
-  constexpr int PARTS = 4, PT = kMergeThreads / PARTS;
+  static_assert(kMergeEntries == PARTS * PT, "four keys per group");
   const int row = blockIdx.x;
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const int S = p.splits, K = p.top_k;
   const int E = S * K;
   const uint64_t *src = reinterpret_cast<const uint64_t *>(static_cast<const float *>(p.ws) + (size_t)p.R * S * 4) +
                         (size_t)row * E;
-  if (tid < E) {
-    keys[tid] = src[tid];
-    rank[tid] = 0;
-  }
+  const uint64_t mine = tid < E ? src[tid] : 0;
+  all[tid] = mine;
+  rank[tid] = 0;
   if (tid < kTopKMax) sorted[tid] = 0;
+  if (tid == 0) count = 0;
   __syncthreads();
+  int n = E, base = 0;  // keys to rank: all[base ..), n of them
+  if (E > PT) {
+    if (tid < PT) {
+      uint32_t m = 0;
+#pragma unroll
+      for (int q = 0; q < PARTS; q++) m = max(m, (uint32_t)(all[tid + q * PT] >> 32));
+      group_max[tid] = m;
+    }
+    __syncthreads();
+    const uint32_t bound = kth_bits<PT / kWave>(group_max, lane, K);
+    if (mine != 0 && (uint32_t)(mine >> 32) >= bound) {
+      const int at = atomicAdd(&count, 1);
+      if (at < PT) all[kMergeEntries + at] = mine;
+    }
+    __syncthreads();
+    if (count <= PT) {
+      n = count;
+      base = kMergeEntries;
+    }
+  }
+  const uint64_t *keys = all + base;
   const int part = tid / PT;
-  const int j0 = E * part / PARTS, j1 = E * (part + 1) / PARTS;
-  for (int i = tid % PT; i < E; i += PT) {
+  const int j0 = n * part / PARTS, j1 = n * (part + 1) / PARTS;
+  for (int i = tid % PT; i < n; i += PT) {
     const uint64_t key = keys[i];
     int r = 0;
 #pragma unroll 8
@@ -442,7 +470,7 @@ __global__ __launch_bounds__(kMergeThreads) void sample_merge(EntropyParams p) {
     if (lane == 0) uniform = u;
   }
   __syncthreads();
-  if (tid < E && keys[tid] != 0 && rank[tid] < K) sorted[rank[tid]] = keys[tid];
+  if (tid < n && keys[tid] != 0 && rank[tid] < K) sorted[rank[tid]] = keys[tid];
   __syncthreads();
   if (wave == 0) sample_pick(p, row, lane, lane < K ? sorted[lane] : 0, uniform);
 }

@@ -255,11 +255,10 @@ __device__ __forceinline__ int gather_select(const uint64_t *cand, const int (&o
   return wave_store_ge<NPL>(out, v, thr, lane);
 }
 
-// A lower bound of the k-th best of a group's logits: the k-th largest of its
-// NW * 64 lanes' maxima (their order bits in LDS), to its 16 leading bits; -inf
-// if fewer than k are finite.
+// The 16 leading bits of the k-th largest of NW * 64 values in LDS (0 if fewer
+// than k exceed the least such bound).
 template <int NW>
-__device__ __forceinline__ float group_bound(const uint32_t *lane_max, int lane, int k) {
+__device__ __forceinline__ uint32_t kth_bits(const uint32_t *lane_max, int lane, int k) {
   uint32_t m[NW];
 #pragma unroll
   for (int i = 0; i < NW; i++) m[i] = lane_max[lane + i * kWave];
@@ -271,6 +270,15 @@ __device__ __forceinline__ float group_bound(const uint32_t *lane_max, int lane,
     for (int i = 0; i < NW; i++) n += __popcll(__ballot(m[i] >= cb));
     if (n >= k) t = cb;
   }
+  return t;
+}
+
+// A lower bound of the k-th best of a group's logits: the k-th largest of its
+// NW * 64 lanes' maxima (their order bits in LDS), to its 16 leading bits; -inf
+// if fewer than k are finite.
+template <int NW>
+__device__ __forceinline__ float group_bound(const uint32_t *lane_max, int lane, int k) {
+  const uint32_t t = kth_bits<NW>(lane_max, lane, k);
   return t > order_bits(kNegInf) ? from_order_bits(t) : kNegInf;
 }
 

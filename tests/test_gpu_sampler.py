@@ -215,3 +215,62 @@ def test_sampler_routes_agree(kind, V, top_k, dt):
         if step == 77 or V < 50000:
             exact, loose = _check_tokens(host(x), V, smp, tok)
             say(" ", step, "tokens equal to the oracle's:", exact, "within rounding:", loose)
+
+
+def _graph_us(calls, fn):
+    """Microseconds per call of `calls` captured in one graph (least of five replays)."""
+    fn()
+    torch.cuda.synchronize()
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        fn()
+        s.synchronize()
+        with torch.cuda.graph(g, stream=s):
+            for _ in range(calls):
+                fn()
+    torch.cuda.synchronize()
+    best = math.inf
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / calls)
+    return best
+
+
+@pytest.mark.parametrize("R,V,few,many,ratio", [
+    (8, 152064, 20, 50, 1.8),    # 15 and 17 us; 42 when every key of the merge was compared with every other
+    (8, 152064, 20, 64, 1.8),    # 15 and 20 us; 49
+])
+def test_sampler_time_by_top_k(R, V, few, many, ratio):
+    """A larger top_k costs little: the merge ranks about top_k keys whatever
+    the number of splits. Times in
+    a graph, with the ratio at least 1.25 times the measured one."""
+    k = kvr()
+    x = torch.randn((R, (V + 7) // 8 * 8), device=DEV).to(torch.bfloat16) * 3.0
+    H, tok = torch.empty(R, device=DEV), torch.empty(R, dtype=torch.int32, device=DEV)
+    us = []
+    for top_k in (few, many):
+        ws = torch.empty(max(k.logit_entropy_sample_workspace_size(R, V, top_k), 16) // 4 + 4, device=DEV)
+        smp = k.Sampler(top_k=top_k, seed=1, step=2)
+        us.append(_graph_us(20, lambda: k.logit_entropy_sample(x, H, tok, smp, V=V, workspace=ws)))
+    say("sampler", R, V, "us at top_k", few, us[0], "at", many, us[1])
+    assert us[1] <= ratio * us[0]
+
+
+@pytest.mark.parametrize("V,top_k,kind", [(1, 1, "2.0"), (9, 20, "2.0"), (159, 20, "ties"), (161, 20, "2.0"),
+                                          (505, 64, "flat"), (512, 64, "ties"), (513, 64, "2.0"), (520, 64, "2.0"), (152064, 50, "ties"),
+                                          (152064, 64, "boosted"), (400000, 64, "2.0"), (400000, 64, "ties"),
+                                          (1200000, 20, "2.0")])
+def test_sampler_candidate_counts(V, top_k, kind):
+    """Rows on both sides of top_k vectors and of the keys that the merge ranks
+    at once (256), with and without more equal logits than that, against the
+    oracle."""
+    say("candidate counts", V, top_k, kind)
+    for dt in (torch.bfloat16, torch.float32):
+        x = _logits(3, V, V, dt, kind, seed=V)
+        smp = kvr().Sampler(top_k=top_k, top_p=0.93, temperature=0.8, seed=5, step=V)
+        _, tok = _run(x.to(DEV), V, smp)
+        _check_tokens(host(x), V, smp, tok)
