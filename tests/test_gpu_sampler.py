@@ -243,10 +243,11 @@ def _graph_us(calls, fn):
 @pytest.mark.parametrize("R,V,few,many,ratio", [
     (8, 152064, 20, 50, 1.8),    # 15 and 17 us; 42 when every key of the merge was compared with every other
     (8, 152064, 20, 64, 1.8),    # 15 and 20 us; 49
+    (64, 100, 12, 13, 1.4),      # 12 vectors: 12 and 12 us; 19 through the register route, without a bound
 ])
 def test_sampler_time_by_top_k(R, V, few, many, ratio):
     """A larger top_k costs little: the merge ranks about top_k keys whatever
-    the number of splits. Times in
+    the number of splits, and rows of fewer than top_k vectors stream. Times in
     a graph, with the ratio at least 1.25 times the measured one."""
     k = kvr()
     x = torch.randn((R, (V + 7) // 8 * 8), device=DEV).to(torch.bfloat16) * 3.0
