@@ -1473,10 +1473,15 @@ void launch_prefix(const AttnParams &p, const EntropyBatch *e, hipStream_t strea
 }
 
 #if !KVR_ATTN_WIDE
-// Four waves per suffix (attn_suffix_split_bf16) where the units are few.
-// Measured, suffixes of 1-512 tokens behind contexts against one wave each:
-// 448 units 12 us less, 1792 5 us less; 3584 of 1-64 tokens 13 us more.
-constexpr long kSplitSuffixUnits = 2048;
+// Four waves per suffix (attn_suffix_split_bf16) where the units are few: two
+// workgroups per CU, each worth one round of waves, so that more units than that
+// gain only by the suffixes' length, which the host does not know. Measured on
+// private contexts (us against one wave each, suffixes of 1 and of 1-512 tokens):
+// 224 units -2.1 / -8.7, 448 -0.3 / -3.2, 672 +3.1 / -1.7, 1344 +5.3 / -2.1, 1792
+// +8.4 / -5.6. Up to kSplitSuffixUnits also where a row has more records than the
+// one-wave kernel folds at once (shared contexts in 16 pieces: 896 units -4.4 /
+// -8.0) or the call's logit rows go along.
+constexpr long kSplitUnits = 512, kSplitSuffixUnits = 2048;
 
 // A logit row takes one wave about as long as the chip needs for this many
 // bytes of caches per logit: 50 us for 152064, 102 with the sampler, against 17
@@ -1613,7 +1618,9 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
   if (e != hipSuccess) return e;
   const size_t pre = (size_t)p.merge_pf * p.merge_blk * sizeof(float);
   constexpr size_t ring = kl_ring<D, kKlTiles, kKlDepth>;
-  if ((long)p.S * p.L * p.Hkv <= kSplitSuffixUnits)
+  const long suffixes = (long)p.S * p.L * p.Hkv;
+  const bool many_records = (p.plen + p.span - 1) / p.span > kFastPieces;
+  if (late || suffixes <= kSplitUnits || (suffixes <= kSplitSuffixUnits && many_records))
     launch_suffix_split<D>(p, late, stream);
   else if constexpr (kSuffixKl)
     hipLaunchKernelGGL((attn_cache_bf16<D, true, kKlTiles, kKlDepth, true>), units, dim3(64), ring + pre, stream, p,

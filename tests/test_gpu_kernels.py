@@ -264,8 +264,11 @@ def test_decode_attn_f32_large_values(D, G, n):
     (2, 1, 1, 2, 6, 128, 4001, 512, torch.bfloat16),
     (3, 3, 1, 1, 16, 64, 16384, 100, torch.bfloat16),
     (64, 8, 10, 4, 4, 64, 700, 30, torch.bfloat16),
-    # Ragged suffixes of 2048 units (the last with four waves each) and of 2112 (one wave each, at D = 128), one and
-    # six context records per row.
+    # Ragged suffixes at D = 128: 512 and 576 units (four waves each, one wave each), 2048 and 2112 with six context
+    # records per row (four waves each, one wave each), and 2112 with one record.
+    (8, 8, 32, 2, 6, 128, 70, 40, torch.bfloat16),
+    (9, 9, 32, 2, 6, 128, 70, 40, torch.bfloat16),
+    (32, 2, 32, 2, 2, 128, 2600, 50, torch.bfloat16),
     (32, 32, 32, 2, 6, 128, 70, 40, torch.bfloat16),
     (33, 11, 32, 2, 6, 128, 70, 40, torch.bfloat16),
     (33, 3, 32, 2, 2, 128, 2600, 50, torch.bfloat16),
@@ -284,6 +287,31 @@ def test_decode_attn_prefix_plans(case):
 ], ids=lambda c: "S%dL%dHkv%dG%dD%d_B%d" % c[:6])
 def test_decode_attn_few_units(case):
     test_decode_attn_base_with_scores(case)
+
+
+def test_decode_attn_prefix_one_wave_suffixes():
+    """Suffixes of 2016 units take the kernel of more than 2048, one wave each:
+    with contexts of one record per row, 36 candidates give the bits that they
+    give among 38. (Four waves each pay for so many units by the suffixes' length
+    only: one-token suffixes behind 600 keys 117 us against 108.)"""
+    k = kvr()
+    L, Hkv, Hq, D, plen, scap = 28, 2, 12, 128, 32, 400
+    g = torch.Generator(device=DEV).manual_seed(9)
+    t = lambda *shape: torch.randn(shape, generator=g, device=DEV).to(torch.bfloat16)  # noqa: E731
+    K, V, PK, PV = t(38, L, Hkv, scap, D), t(38, L, Hkv, scap, D), t(38, L, Hkv, plen, D), t(38, L, Hkv, plen, D)
+    q, kn, vn = t(38, L, Hq, D), t(38, L, Hkv, D), t(38, L, Hkv, D)
+    lens = torch.randint(1, scap + 1, (38,), generator=g, device=DEV, dtype=torch.int32)
+    outs = []
+    for S in (36, 38):
+        cache, prefix = k.Cache(K[:S].clone(), V[:S].clone(), None), k.Prefix(PK[:S].clone(), PV[:S].clone())
+        ws = torch.empty(k.decode_attn_workspace_size(cache, prefix, Hq) // 4 + 4, dtype=torch.float32, device=DEV)
+        out = torch.empty((S, L, Hq, D), dtype=torch.bfloat16, device=DEV)
+        say("suffixes of", S * L * Hkv, "units")
+        k.decode_attn(cache, lens[:S].clone(), q[:S].clone(), out, 1.0 / math.sqrt(D), k_new=kn[:S].clone(),
+                      v_new=vn[:S].clone(), prefix=prefix, workspace=ws)
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int16), outs[1][:36].view(torch.int16))
 
 
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])

@@ -16,7 +16,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import host, say
+from gpu_util import graph_us, host, say
 from oracle import sampler as osamp
 
 pytestmark = pytest.mark.gpu
@@ -217,29 +217,6 @@ def test_sampler_routes_agree(kind, V, top_k, dt):
             say(" ", step, "tokens equal to the oracle's:", exact, "within rounding:", loose)
 
 
-def _graph_us(calls, fn):
-    """Microseconds per call of `calls` captured in one graph (least of five replays)."""
-    fn()
-    torch.cuda.synchronize()
-    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
-    with torch.cuda.stream(s):
-        fn()
-        s.synchronize()
-        with torch.cuda.graph(g, stream=s):
-            for _ in range(calls):
-                fn()
-    torch.cuda.synchronize()
-    best = math.inf
-    for _ in range(5):
-        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        a.record()
-        g.replay()
-        b.record()
-        torch.cuda.synchronize()
-        best = min(best, a.elapsed_time(b) * 1e3 / calls)
-    return best
-
-
 @pytest.mark.parametrize("R,V,few,many,ratio", [
     (8, 152064, 20, 50, 1.8),    # 15 and 17 us; 42 when every key of the merge was compared with every other
     (8, 152064, 20, 64, 1.8),    # 15 and 20 us; 49
@@ -256,7 +233,7 @@ def test_sampler_time_by_top_k(R, V, few, many, ratio):
     for top_k in (few, many):
         ws = torch.empty(max(k.logit_entropy_sample_workspace_size(R, V, top_k), 16) // 4 + 4, device=DEV)
         smp = k.Sampler(top_k=top_k, seed=1, step=2)
-        us.append(_graph_us(20, lambda: k.logit_entropy_sample(x, H, tok, smp, V=V, workspace=ws)))
+        us.append(graph_us(20, lambda: k.logit_entropy_sample(x, H, tok, smp, V=V, workspace=ws)))
     say("sampler", R, V, "us at top_k", few, us[0], "at", many, us[1])
     assert us[1] <= ratio * us[0]
 
