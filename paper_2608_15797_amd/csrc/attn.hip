@@ -496,6 +496,15 @@ constexpr size_t kl_ring = (size_t)DEPTH * 16 * TILES * D * 2;
 constexpr int kKlTiles = 2;
 constexpr int kKlDepth = 2;
 
+// A logit row by a group of NW waves, for the logit type LT below.
+template <int LT, int NW>
+__device__ __forceinline__ void entropy_any_row_group(const EntropyParams &p, int row, int lane, int wave, uint64_t *lds) {
+  if constexpr (LT == 1) entropy_row_group<bf16_t, 12, NW>(p, row, lane, wave, reinterpret_cast<Tri *>(lds));
+  else if constexpr (LT == 2) entropy_row_group<float, 6, NW>(p, row, lane, wave, reinterpret_cast<Tri *>(lds));
+  else if constexpr (LT == 3) entropy_sample_row_group<bf16_t, 8, NW>(p, row, lane, wave, lds);
+  else entropy_sample_row_group<float, 4, NW>(p, row, lane, wave, lds);
+}
+
 // LT (evicted cache only): 0, or the logit type of the step's entropy rows
 // computed in the same launch (1 = bfloat16, 2 = float32; 3 and 4 the same
 // with the sampler). The first e.row0[e.nsets] workgroups of the grid are
@@ -504,22 +513,29 @@ constexpr int kKlDepth = 2;
 // row's next token from its k best logits, using the launch's LDS for the
 // candidates); they are dispatched first and stream their rows while the
 // attention units run. The other workgroups are the attention units.
-template <int D, bool MERGE, int TILES, int DEPTH, bool KL = false, int LT = 0>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void attn_cache_bf16(AttnParams p,
-                                                                                               EntropyBatch e) {
+// NWG = 4 (with rows): workgroups of four waves, a logit row by all four or four
+// units by one wave each, in LDS of p.wave_lds bytes per wave. A unit's
+// arithmetic is that of NWG = 1.
+template <int D, bool MERGE, int TILES, int DEPTH, bool KL, int LT, int NWG>
+__device__ __forceinline__ void attn_cache_wave(const AttnParams &p, const EntropyBatch &e) {
   static_assert(!(LT && MERGE), "entropy rows ride with the evicted cache");
+  static_assert(NWG == 1 || (KL && LT), "groups of waves for logit rows beside key rings");
   constexpr int CH = 16 * TILES;
   constexpr int NB = Geo<D>::NB;
   constexpr uint32_t ROW = D * 2;
-  extern __shared__ float smem[];
+  extern __shared__ float smem_all[];
+  const int wave = NWG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  float *smem = smem_all + (NWG == 1 ? 0 : wave * (p.wave_lds / (int)sizeof(float)));
 
   int unit = blockIdx.x;  // ((s * L) + l) * Hkv + h
   if constexpr (LT != 0) {
     const int rows = e.row0[e.nsets];
     if (unit < rows) {
       const int k = batch_set(e, unit);
-      uint64_t *cand = reinterpret_cast<uint64_t *>(smem);
-      if constexpr (LT == 1)
+      uint64_t *cand = reinterpret_cast<uint64_t *>(smem_all);
+      if constexpr (NWG > 1)
+        entropy_any_row_group<LT, NWG>(e.set[k], unit - e.row0[k], threadIdx.x % kWave, wave, cand);
+      else if constexpr (LT == 1)
         entropy_row_wave<bf16_t, 12>(e.set[k], unit - e.row0[k], threadIdx.x);
       else if constexpr (LT == 2)
         entropy_row_wave<float, 6>(e.set[k], unit - e.row0[k], threadIdx.x);
@@ -530,12 +546,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void at
       return;
     }
     unit -= rows;
+    if constexpr (NWG > 1) {
+      unit = unit * NWG + wave;
+      if (unit >= p.S * p.L * p.Hkv) return;  // no barrier below
+    }
   }
   const int h = unit % p.Hkv;
   const int sl = unit / p.Hkv;
   const int l = sl % p.L;
   const int s = sl / p.L;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x % kWave;
   const int r16 = lane & 15;
   const int g4 = lane >> 4;
   const int G = p.G;
@@ -823,7 +843,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void at
         stat[r16] = st.m;
         stat[16 + r16] = 1.0f / z;
       }
-      __syncthreads();
+      if constexpr (NWG == 1) __syncthreads();
+      else wave_lds_sync();
       // Slot n-1 (the new token) and the first window step store; older slots
       // add to the stored score (prefetched above for the first PRE*64 slots).
 #pragma unroll
@@ -844,7 +865,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void at
   }
 }
 
+template <int D, bool MERGE, int TILES, int DEPTH, bool KL = false, int LT = 0>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void attn_cache_bf16(AttnParams p,
+                                                                                               EntropyBatch e) {
+  attn_cache_wave<D, MERGE, TILES, DEPTH, KL, LT, 1>(p, e);
+}
+
 #if !KVR_ATTN_WIDE
+template <int D, int LT, int NWG>
+__global__ __launch_bounds__(64 * NWG) __attribute__((amdgpu_waves_per_eu(2))) void attn_cache_groups_bf16(
+    AttnParams p, EntropyBatch e) {
+  attn_cache_wave<D, false, kKlTiles, kKlDepth, true, LT, NWG>(p, e);
+}
+
 // Suffix kernel of launches of few units (the suffixes of a few helper
 // contexts): kSplitWaves waves per unit, each with every kSplitWaves-th chunk
 // of 16 keys through a key ring of its own. Bound by the length of a unit's
@@ -885,12 +918,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
     const int rows = e.row0[e.nsets];
     if (unit < rows) {
       const int k = batch_set(e, unit), row = unit - e.row0[k];
-      if constexpr (LT == 1) entropy_row_group<bf16_t, 12, NW>(e.set[k], row, lane, wave, reinterpret_cast<Tri *>(smem));
-      else if constexpr (LT == 2) entropy_row_group<float, 6, NW>(e.set[k], row, lane, wave, reinterpret_cast<Tri *>(smem));
-      else if constexpr (LT == 3)
-        entropy_sample_row_group<bf16_t, 8, NW>(e.set[k], row, lane, wave, reinterpret_cast<uint64_t *>(smem));
-      else
-        entropy_sample_row_group<float, 4, NW>(e.set[k], row, lane, wave, reinterpret_cast<uint64_t *>(smem));
+      entropy_any_row_group<LT, NW>(e.set[k], row, lane, wave, reinterpret_cast<uint64_t *>(smem));
       return;
     }
     unit -= rows;
@@ -1487,13 +1515,18 @@ constexpr long kSplitUnits = 512, kSplitSuffixUnits = 2048;
 // bytes of caches per logit: 50 us for 152064, 102 with the sampler, against 17
 // and 29 for a workgroup of four waves (64 rows each).
 constexpr double kRowBytes = 1900, kSampleRowBytes = 3800;
-// One-wave rows of an evicted-cache launch are worth a launch of their own,
-// four waves per row, where its units take less than this share of a row
-// (their bytes at full caches): 64 rows with 256 units 51 us in the launch and 29
-// apart, with 1024 (143 MB) 57 and 38, with 1536 (214 MB) 59 and 46; sampled, with 1024 units
-// 102 and 51, with 2048 104 and 66. With 7168 units sampled rows cost 5 us in
-// the launch.
-constexpr double kOwnShare = 0.8;
+// One-wave rows of an evicted-cache launch give way to rows of four waves where
+// its units take less than a share of a row (their bytes at full caches, at least
+// 10 us' worth, the shortest launch). Up to kGroupUnits units (four per CU) the
+// launch then has workgroups of four waves for rows and units alike: 64 rows of
+// 152064 with 512 units 53 us with a wave each and 20 so, with 1024 (143 MB) 59 and
+// 29; sampled 134 and 33, 136 and 36; one row of 16384 with 4 units 9.9 either
+// way, of 32000 15.0 and 10.6. Beyond that the rows get a launch of their own before
+// the units: with 1536 (214 MB) 61 and 46; sampled, with 2048 137 and 68. With 7168
+// units sampled rows cost 5 us in the launch.
+constexpr double kOwnShare = 0.8, kGroupShare = 1.5, kLeastBytes = 55e6;
+constexpr unsigned kGroupUnits = 1024;
+constexpr size_t kCuLds = 160 * 1024;  // LDS of a CU, all of which one workgroup may take
 
 // Whether one-wave rows take longer than a launch that reads `bytes` takes `share` of.
 bool rows_outlast(const EntropyBatch &e, double bytes, double share) {
@@ -1569,6 +1602,21 @@ void launch_own(const AttnParams &p, const EntropyBatch *e, size_t lds, hipStrea
     hipLaunchKernelGGL((attn_cache_bf16<D, false, TILES, DEPTH, KL, 1>), grid, dim3(64), lds, stream, p, *e);
 }
 
+// The same in workgroups of four waves, for few units: a row each, or four units.
+template <int D>
+void launch_own_groups(AttnParams p, const EntropyBatch &e, size_t wave_lds, hipStream_t stream) {
+  p.wave_lds = (int)wave_lds;
+  const dim3 grid(e.row0[e.nsets] + (p.S * p.L * p.Hkv + kSplitWaves - 1) / kSplitWaves), block(64 * kSplitWaves);
+  const size_t lds = kSplitWaves * wave_lds;
+  const bool f32 = e.set[0].dtype == 0, sample = e.set[0].top_k > 0;
+  static_assert(kSplitWaves * kl_ring<64, kKlTiles, kKlDepth> >= kSampleGroupLds<kSplitWaves>, "the rows' candidates fit");
+  constexpr int W = kSplitWaves;
+  if (sample && f32) hipLaunchKernelGGL((attn_cache_groups_bf16<D, 4, W>), grid, block, lds, stream, p, e);
+  else if (sample) hipLaunchKernelGGL((attn_cache_groups_bf16<D, 3, W>), grid, block, lds, stream, p, e);
+  else if (f32) hipLaunchKernelGGL((attn_cache_groups_bf16<D, 2, W>), grid, block, lds, stream, p, e);
+  else hipLaunchKernelGGL((attn_cache_groups_bf16<D, 1, W>), grid, block, lds, stream, p, e);
+}
+
 template <int D>
 hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStream_t stream) {
   AttnParams p = p_in;
@@ -1589,7 +1637,13 @@ hipError_t launch_bf16(const AttnParams &p_in, const EntropyBatch *ent, hipStrea
     const size_t logits = p.scores ? ((size_t)p.G * ((p.cap + 63) & ~63) + 32) * sizeof(float) : 0;
     const size_t lds_min = D == 128 ? kBaseLdsFloor : 0;
     constexpr size_t ring = kl_ring<D, kKlTiles, kKlDepth>;
-    if (ent && rows_outlast(*ent, (double)units.x * p.cap * (4 * D), kOwnShare)) {
+    const bool groups = units.x <= kGroupUnits && kSplitWaves * (ring + logits) <= kCuLds;
+    const double bytes = (double)units.x * p.cap * (4 * D);
+    if (ent && rows_outlast(*ent, bytes > kLeastBytes ? bytes : kLeastBytes, groups ? kGroupShare : kOwnShare)) {
+      if (groups) {
+        launch_own_groups<D>(p, *ent, ring + logits, stream);
+        return hipGetLastError();
+      }
       launch_rows(*ent, stream);
       ent = nullptr;
     }

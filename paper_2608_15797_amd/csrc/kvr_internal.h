@@ -38,6 +38,7 @@ struct AttnParams {
   // partials into LDS (merge_blk floats per piece) at wave start.
   int merge_pf, merge_blk;
   int rows_late;  // the call's logit rows go with the suffix launch (rows_with_suffix)
+  int wave_lds;   // bytes of LDS per wave where units share a workgroup
 };
 
 // Work plan of the prefix path (rows = C * G query rows per prefix unit;

@@ -23,7 +23,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import as_f64, host, rowwise_rel_err, say
+from gpu_util import as_f64, graph_us, host, rowwise_rel_err, say
 
 pytestmark = pytest.mark.gpu
 
@@ -37,10 +37,15 @@ CASES = [
      [(5, 1023, 1024, 2.0, 1.0, True), (3, 5, 8, 1.0, 1.0, False), (2, 8, 8, 0.5, 2.0, True)]),
     ((2, 1, 2, 4, 64, 12, 4, 6, torch.bfloat16), torch.bfloat16, [(7, 50000, 50000, 2.0, 1.0, True)]),
     ((1, 1, 1, 4, 64, 16, 8, 16, torch.float32), torch.float32, [(1, 1024, 1024, 2.0, 1.0, True)]),
-    # 640 units: long rows get a launch of their own, short ones a wave of the attention launch each.
+    # 640 units: long rows and four units each share workgroups of four waves, short rows get a wave each.
     ((16, 10, 4, 7, 128, 64, 32, 64, torch.bfloat16), torch.bfloat16, [(6, 152064, 152064, 3.0, 1.0, True)]),
     ((16, 10, 4, 4, 64, 64, 32, 64, torch.bfloat16), torch.float32,
      [(5, 1023, 1024, 2.0, 1.0, True), (3, 8, 8, 1.0, 1.0, False)]),
+    # 21 units (a workgroup with one), caches whose groups' logits take most of a CU's LDS; 1100 units: rows in a launch
+    # of their own.
+    ((7, 3, 1, 16, 64, 64, 32, 64, torch.bfloat16), torch.float32, [(3, 60000, 60000, 2.0, 1.0, True)]),
+    ((3, 3, 1, 16, 128, 128, 32, 180, torch.bfloat16), torch.bfloat16, [(3, 60000, 60000, 2.0, 1.0, True)]),
+    ((11, 25, 4, 2, 64, 64, 32, 64, torch.bfloat16), torch.bfloat16, [(5, 152064, 152064, 3.0, 1.0, True)]),
 ]
 
 
@@ -152,11 +157,14 @@ SAMPLE_CASES = [
     ((3, 2, 2, 8, 128, 16, 4, 8, torch.bfloat16), torch.float32,
      [(5, 1023, 1024, 2.0), (3, 5, 8, 1.0), (2, 8, 8, "flat")], (1.0, 64, 1.0, 9, 0)),
     ((1, 1, 1, 4, 64, 16, 8, 16, torch.float32), torch.bfloat16, [(4, 1024, 1024, 2.0)], (0.5, 1, 0.5, 3, 2)),
-    # 640 units: long rows in a launch of their own, short ones in the attention launch.
+    # 640 units: long rows beside four units each in workgroups of four waves, short ones a wave each.
     ((16, 10, 4, 7, 128, 64, 32, 64, torch.bfloat16), torch.bfloat16,
      [(6, 152064, 152064, "boosted"), (3, 30000, 30000, "ties")], (0.8, 20, 0.95, 1234, 7)),
     ((16, 10, 4, 4, 64, 64, 32, 64, torch.bfloat16), torch.float32,
      [(5, 1023, 1024, 2.0), (3, 5, 8, 1.0)], (0.8, 50, 0.95, 4, 1)),
+    ((7, 3, 1, 8, 128, 64, 32, 64, torch.bfloat16), torch.float32, [(3, 60000, 60000, 2.0)], (0.8, 20, 0.95, 5, 2)),
+    ((11, 25, 4, 2, 64, 64, 32, 64, torch.bfloat16), torch.bfloat16, [(5, 152064, 152064, "boosted")],
+     (0.8, 20, 0.95, 6, 3)),
 ]
 
 
@@ -329,3 +337,22 @@ def test_decode_attn_entropy_with_prefix(ci):
             assert (got == ref_tok.cpu().numpy()).all(), (j, got, ref_tok.cpu().numpy())
             exact, loose = _check_tokens(host(x), V_, smp, got)
             say("  set", j, "tokens oracle-exact", exact, "near-threshold", loose)
+
+
+@pytest.mark.parametrize("V", [1000, 8192])
+def test_short_rows_ride_in_the_launch(V):
+    """Rows that one wave reads within the shortest attention launch get no
+    launch of their own: with 4 units the call takes as long as the attention
+    alone (9.6 and 9.8 us; 13.6 and 14.0 with a launch before it). Times in a
+    graph, least of five; 1.2 lies between the two."""
+    from paper_2608_15797_amd import kvr as k
+    say("short rows in the launch", V)
+    t = lambda *shape: torch.randn(shape, device=DEV).to(torch.bfloat16)  # noqa: E731
+    cache = k.Cache(t(1, 1, 4, 272, 128), t(1, 1, 4, 272, 128), None)
+    q, out = t(1, 1, 28, 128), t(1, 1, 28, 128)
+    lens = torch.full((1,), 200, dtype=torch.int32, device=DEV)
+    ls = k.LogitSet(t(1, V), torch.zeros(1, device=DEV), V)
+    alone = graph_us(20, lambda: k.decode_attn(cache, lens, q, out, 0.1))
+    both = graph_us(20, lambda: k.decode_attn_entropy(cache, lens, q, out, 0.1, [ls]))
+    say("  us alone", alone, "with the row", both)
+    assert both <= 1.2 * alone
