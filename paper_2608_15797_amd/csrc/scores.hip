@@ -581,7 +581,10 @@ struct Window {
   template <bool REF>
   __device__ __forceinline__ void normalise(int row0, int tiles) const {
     const int slots = (tiles + kNW - 1) / kNW;  // per wave, at most kRowTiles
-    if (slots <= 2) fresh().template normalisers<2, REF>(row0, 0);
+    // Few rows wait for the keys' stream more than for their products, so one
+    // tile has a form of its own: 112 heads of 800 keys and 128 rows 121 -> 110 us.
+    if (slots <= 1) fresh().template normalisers<1, REF>(row0, 0);
+    else if (slots <= 2) fresh().template normalisers<2, REF>(row0, 0);
     else if (slots <= 4) fresh().template normalisers<4, REF>(row0, 0);
     else if constexpr (!REF) fresh().template normalisers<kRowTiles, REF>(row0, 0);
     else {
